@@ -394,27 +394,49 @@ __device__ __forceinline__ void fft_pass(cplx (&v)[NF][P], int t,
     }
 }
 
-template <int N, int P, bool INV, int NF, int I, bool TWD, class Lds>
+// Orders the LDS exchange of a transform's threads: the whole workgroup, or
+// (WAVE) only the wavefront that holds all of them.  LDS serves a wavefront's
+// accesses in the order they were issued, so within one wavefront nothing has
+// to wait: the fence only keeps the compiler from moving LDS accesses across.
+template <bool WAVE>
+__device__ __forceinline__ void exchange_sync() {
+    if constexpr (WAVE) {
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront", "local");
+        __builtin_amdgcn_wave_barrier();
+    } else {
+        __syncthreads();
+    }
+}
+
+// Whether T threads per transform, numbered consecutively from a multiple of
+// T, always lie in one wavefront.
+constexpr bool in_one_wave(int T) { return T <= 64 && 64 % T == 0; }
+
+template <int N, int P, bool INV, int NF, int I, bool TWD, bool WAVE, class Lds>
 __device__ __forceinline__ void fft_from(cplx (&v)[NF][P], int t,
                                          const cplx* __restrict__ tw, const Lds& lds) {
     using S = FftShape<N, P>;
     fft_pass<N, P, I, INV, NF, TWD>(v, t, tw, lds);
     if constexpr (I + 1 < S::NP) {
-        __syncthreads();
+        exchange_sync<WAVE>();
 #pragma unroll
         for (int f = 0; f < NF; ++f) lds_load_points<N, P>(lds, f, t, v[f]);
-        __syncthreads();
-        fft_from<N, P, INV, NF, I + 1, TWD>(v, t, tw, lds);
+        exchange_sync<WAVE>();
+        fft_from<N, P, INV, NF, I + 1, TWD, WAVE>(v, t, tw, lds);
     }
 }
 
 // Full transform.  Every thread of the workgroup must call this (barriers).
 // TWD: read every twiddle of a butterfly from the table (a table in LDS),
 // instead of the one to three table reads and the products of `twiddles`.
-template <int N, int P, bool INV, int NF, bool TWD = false, class Lds>
+// WAVE: the transform's threads lie in one wavefront (in_one_wave) and share
+// its LDS slots with no other; there are then no workgroup barriers, and the
+// wavefronts of a block run through their transforms independently.
+template <int N, int P, bool INV, int NF, bool TWD = false, bool WAVE = false, class Lds>
 __device__ __forceinline__ void fft_run(cplx (&v)[NF][P], int t,
                                         const cplx* __restrict__ tw, const Lds& lds) {
-    fft_from<N, P, INV, NF, 0, TWD>(v, t, tw, lds);
+    static_assert(!WAVE || in_one_wave(N / P), "a transform's threads span wavefronts");
+    fft_from<N, P, INV, NF, 0, TWD, WAVE>(v, t, tw, lds);
 }
 
 // ------------------------------------------- sequential LDS exchange -----

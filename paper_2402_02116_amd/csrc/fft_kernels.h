@@ -117,7 +117,14 @@ __global__ __launch_bounds__(256) void k_rows(const cplx* in, cplx* out,
     }
     // idle threads (block padded to whole waves) work in a dummy slot F
     RowLds lds{lds_dyn + (size_t)(q < F ? q : F) * PL};
-    fft_run<N, P, INV, 1>(v, t, tw, lds);
+    // A row's threads lie in one wavefront (up to 32 of them; one row per
+    // wavefront was slower than with workgroup barriers: 1.32 against 1.25 ms
+    // for the inverse pass at 1024^2 x 128): no workgroup barriers in the
+    // transform.  The forward pass then waits once before its stores, because
+    // neighbouring rows write parts of the same cache lines of a tiled spectrum.
+    constexpr bool kWave = in_one_wave(T) && T <= 32;
+    fft_run<N, P, INV, 1, false, kWave>(v, t, tw, lds);
+    if constexpr (!INV && kWave) __syncthreads();
 
     double acc[kPartialNV] = {};
     if (active) {

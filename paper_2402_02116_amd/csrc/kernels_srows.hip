@@ -248,7 +248,9 @@ __global__ __launch_bounds__(NT) void k_srows(const cplx* __restrict__ u, const 
 
     // 3. forward row transforms (idle threads work in a dummy slot)
     RowLdsF lds{lds_dyn + (size_t)(active ? q : 2 * F) * PL};
-    fft_run<N, P, false, 1>(v, t, tw, lds);
+    constexpr bool kWave = in_one_wave(T) && T <= 32;   // as in k_rows
+    fft_run<N, P, false, 1, false, kWave>(v, t, tw, lds);
+    if constexpr (kWave) __syncthreads();   // rows share cache lines of the tiled spectrum
     if (active) {   // the spectrum: row-major or column-tiled
         cplx* o = out + so + c * plane;
         const int tnz = pd.tile_sh ? nz : 0;
