@@ -10,8 +10,8 @@
 // is therefore loaded from and stored to global memory in coalesced
 // t-fastest order, and only the passes in between go through LDS.
 //
-// The radix sequence is chosen at compile time from {32, 16, 8, 4, 2, 3, 5};
-// every radix must divide P.  Twiddles come from a length-N table
+// The radix sequence is chosen at compile time from {32, 24, 20, 16, 12, 10,
+// 8, 4, 2, 3, 5}; every radix must divide P.  Twiddles come from a length-N table
 // tw[m] = exp(-2 pi i m / N) (double-rounded on the host); the inverse uses
 // conjugates.  No normalisation is applied in either direction.
 #pragma once
@@ -26,11 +26,11 @@ struct RadixPlan {
 
 constexpr RadixPlan radix_plan(int N, int P) {
     RadixPlan pl{0, {0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0}};
-    const int cand[7] = {32, 16, 8, 4, 2, 3, 5};
+    const int cand[11] = {32, 24, 20, 16, 12, 10, 8, 4, 2, 3, 5};
     int rem = N;
     while (rem > 1) {
         int pick = 0;
-        for (int i = 0; i < 7; ++i) {
+        for (int i = 0; i < 11; ++i) {
             if (P % cand[i] == 0 && rem % cand[i] == 0) { pick = cand[i]; break; }
         }
         if (pick == 0 || pl.np == 16) { pl.np = -1; return pl; }
@@ -260,6 +260,43 @@ __device__ __forceinline__ void dft5(cplx& x0, cplx& x1, cplx& x2, cplx& x3, cpl
     x3 = csub(a2, b2);
 }
 
+// A DFT of length N1 N2 for coprime N1, N2 by the prime-factor algorithm
+// (Good, 1958): with n = N2 n1 + N1 n2 and k = N2 (N2^-1 mod N1) k1 + N1
+// (N1^-1 mod N2) k2 (mod N1 N2) the kernel factors into W_N1^(n1 k1)
+// W_N2^(n2 k2), so the two stages need no twiddle factors between them.  One
+// pass of radix 12 (or 10, 20, 24) takes the place of passes of 4 and 3 (2
+// and 5, ...) and their exchange through LDS.
+constexpr int mod_inverse(int a, int m) {
+    for (int i = 1; i < m; ++i)
+        if (a * i % m == 1) return i;
+    return 1;
+}
+
+template <int R, bool INV>
+__device__ __forceinline__ void dft(cplx (&x)[R]);
+
+template <int N1, int N2, bool INV>
+__device__ __forceinline__ void dft_pfa(cplx (&x)[N1 * N2]) {
+    constexpr int N = N1 * N2;
+    cplx y[N1][N2];
+#pragma unroll
+    for (int n2 = 0; n2 < N2; ++n2) {
+        cplx a[N1];
+#pragma unroll
+        for (int n1 = 0; n1 < N1; ++n1) a[n1] = x[(N2 * n1 + N1 * n2) % N];
+        dft<N1, INV>(a);
+#pragma unroll
+        for (int k1 = 0; k1 < N1; ++k1) y[k1][n2] = a[k1];
+    }
+#pragma unroll
+    for (int k1 = 0; k1 < N1; ++k1) {
+        dft<N2, INV>(y[k1]);
+#pragma unroll
+        for (int k2 = 0; k2 < N2; ++k2)
+            x[(N2 * mod_inverse(N2 % N1, N1) * k1 + N1 * mod_inverse(N1 % N2, N2) * k2) % N] = y[k1][k2];
+    }
+}
+
 template <int R, bool INV>
 __device__ __forceinline__ void dft(cplx (&x)[R]) {
     if constexpr (R == 2) dft2<INV>(x[0], x[1]);
@@ -267,6 +304,10 @@ __device__ __forceinline__ void dft(cplx (&x)[R]) {
     else if constexpr (R == 5) dft5<INV>(x[0], x[1], x[2], x[3], x[4]);
     else if constexpr (R == 4) dft4<INV>(x[0], x[1], x[2], x[3]);
     else if constexpr (R == 8) dft8<INV>(x);
+    else if constexpr (R == 10) dft_pfa<2, 5, INV>(x);
+    else if constexpr (R == 12) dft_pfa<4, 3, INV>(x);
+    else if constexpr (R == 20) dft_pfa<4, 5, INV>(x);
+    else if constexpr (R == 24) dft_pfa<8, 3, INV>(x);
     else if constexpr (R == 16) dft16<INV>(x);
     else if constexpr (R == 32) dft32<INV>(x);
     else static_assert(R == 2, "unsupported radix");
@@ -274,7 +315,7 @@ __device__ __forceinline__ void dft(cplx (&x)[R]) {
 
 // --------------------------------------------------------------- twiddles --
 // w[r] = W^(r e) for r = 1..R-1, where W^e = tw[e] (forward; conjugated for
-// the inverse).  Only W^e, for R >= 8 W^(4e) and for R = 32 W^(16e) are read
+// the inverse).  Only W^e, for R >= 8 W^(4e) and for R >= 20 W^(16e) are read
 // from the table; the other powers are products of at most five factors (a
 // few ulp).
 template <int R, bool INV>
@@ -292,23 +333,24 @@ __device__ __forceinline__ void twiddles(cplx (&w)[R], const cplx* __restrict__ 
 #pragma unroll
         for (int r = 5; r < 8; ++r) w[r] = cmul(w4, w[r - 4]);
     }
-    if constexpr (R >= 16) {
+    if constexpr (R >= 10) {
         const cplx w8 = cmul(w[4], w[4]);
-        const cplx w12 = cmul(w8, w[4]);
         w[8] = w8;
-        w[12] = w12;
 #pragma unroll
-        for (int r = 1; r < 4; ++r) {
-            w[8 + r] = cmul(w8, w[r]);
-            w[12 + r] = cmul(w12, w[r]);
+        for (int r = 9; r < 12 && r < R; ++r) w[r] = cmul(w8, w[r - 8]);
+        if constexpr (R >= 16) {
+            const cplx w12 = cmul(w8, w[4]);
+            w[12] = w12;
+#pragma unroll
+            for (int r = 13; r < 16; ++r) w[r] = cmul(w12, w[r - 12]);
         }
     }
-    if constexpr (R == 32) {
+    if constexpr (R >= 20) {
         cplx w16 = tw[16 * e];
         if (INV) w16 = cconj(w16);
         w[16] = w16;
 #pragma unroll
-        for (int r = 1; r < 16; ++r) w[16 + r] = cmul(w16, w[r]);
+        for (int r = 17; r < R; ++r) w[r] = cmul(w16, w[r - 16]);
     }
 }
 
