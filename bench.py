@@ -667,12 +667,12 @@ def normal_cg(a):
 
 
 # algorithmic bytes per cell-system of the 3-D passes (complex64, three
-# components: 24 B per field): stencil u -> b; x transforms; the y forward, z
-# forward-Green-inverse and y inverse transforms (three kernels); inverse x
-# transforms reading the spectrum and u and writing A u
-PASS3_BYTES = (48.0, 48.0, 3 * 48.0, 72.0)
-PASS3_NAMES = ("k_stencil3 (contrast stencil, six strains)", "k_rows (x transforms)",
-               "k_axis y / z with 3x3 G_hat / y (three kernels)", "k_rows (inverse x transforms + LS epilogue)")
+# components: 24 B per field): stencil u -> b; x and y transforms by planes;
+# the z forward-Green-inverse transforms; inverse y and x transforms reading
+# the spectrum and u and writing A u
+PASS3_BYTES = (48.0, 48.0, 48.0, 72.0)
+PASS3_NAMES = ("k_stencil3 (contrast stencil, six strains)", "k_plane_fwd (x and y transforms)",
+               "k_axis (z with 3x3 G_hat)", "k_plane_inv (inverse x and y transforms + LS epilogue)")
 
 
 def hess3d(a):

@@ -88,7 +88,8 @@ struct ProbHost {
     size_t map_off;       // floats into the maps region
     size_t data_off;      // complex elements into plan-level receiver data
     int nrec;
-    int np_rows;          // partial records per system from the row epilogues
+    int np_rows;          // partial records per system from the inverse pass's BiCGSTAB epilogues
+    int np_gm;            // ... from its GMRES epilogues
     int np_vec;           // partial records per system from vector kernels
     KernelCfg cfg;        // kernel variants (defaults, the autotuner's or the caller's)
     float tuned_us[4];    // autotune: stencil, row, column, stencil + rows time of the choice
@@ -96,6 +97,7 @@ struct ProbHost {
     bool d3 = false;      // a 3-D problem (fwils_plan_create3)
     int ny = 1, ncomp = 2, nmaps = 5;
     int rps = 0;          // rows of nx points per system: ncomp nz ny
+    bool planes = false;  // 3-D: the x and y transforms are one pass over whole planes
     size_t cells = 0;     // nx ny nz
     ProbDev3 dev3{};      // 3-D kernel constants
 };
@@ -227,19 +229,55 @@ inline ProbDev3 view3(const ProbHost& P, const ProbDev& d) {
     return d3;
 }
 
-// The part of a convolution between the forward and the inverse x (row)
-// transforms, in place on the spectrum tmp: 2-D, the column pass with the
-// Green multiply; 3-D, the y transforms around the z pass with the 3 x 3
-// Green multiply.  d: the view (its nsys systems from tmp on).
-hipError_t spectral(fwils_plan pl, const ProbHost& P, const ProbDev& d, cplx* tmp, const SysState* st, hipStream_t s) {
+// Whether a convolution that ends in epilogue epi takes the plane passes (3-D
+// plans whose planes have them; the GMRES epilogues exist in the row pass
+// only).  All passes of a convolution must agree: the spectrum's order differs.
+inline bool by_planes(const ProbHost& P, int epi) {
+    return P.planes && epi != EPI_ARNOLDI && epi != EPI_GMRES_R0;
+}
+
+// The forward x (row) transforms of d.nsys systems, in into the spectrum tmp;
+// with the y transforms where the planes are one pass.  epi: the epilogue
+// that will end the convolution.
+hipError_t forward_pass(fwils_plan pl, const ProbHost& P, const ProbDev& d, int epi, const cplx* in, cplx* tmp,
+                        const SysState* st, hipStream_t s) {
+    if (by_planes(P, epi)) {
+        const int pps = P.rps / P.ny;
+        return launch_plane(P.p.nx, P.ny, PLANE_FWD, in, tmp, nullptr, nullptr, nullptr, d.nsys * pps, pps,
+                            const_cast<SysState*>(st), pl->tw, s);
+    }
+    return launch_rows_fwd(P.p.nx, P.cfg.row_p, in, tmp, d.nsys * P.rps, P.rps, tile_rows(d), st, pl->tw, s);
+}
+
+// The part of a convolution between the forward and the inverse pass, in
+// place on the spectrum tmp: 2-D, the column pass with the Green multiply;
+// 3-D, the z pass with the 3 x 3 Green multiply, and around it the y
+// transforms that are not part of those passes.
+hipError_t spectral(fwils_plan pl, const ProbHost& P, const ProbDev& d, int epi, cplx* tmp, const SysState* st,
+                    hipStream_t s) {
     if (!P.d3) return launch_cols(COL_GREEN, P.cfg.col, tmp, d, st, pl->tw, s);
     const ProbDev3 d3 = view3(P, d);
     const int nx = d3.nx, ny = d3.ny, nz = d3.nz;
+    const bool planes = by_planes(P, epi), ypass = ny > 1 && !planes;
     hipError_t e = hipSuccess;
-    if (ny > 1) e = launch_axis3(AX_FWD, ny, tmp, nx, d3.nsys * 3 * nz, 3 * nz, st, pl->tw, d3, s);
-    if (e == hipSuccess) e = launch_axis3(AX_GREEN, nz, tmp, nx * ny, d3.nsys, 1, st, pl->tw, d3, s);
-    if (e == hipSuccess && ny > 1) e = launch_axis3(AX_INV, ny, tmp, nx, d3.nsys * 3 * nz, 3 * nz, st, pl->tw, d3, s);
+    if (ypass) e = launch_axis3(AX_FWD, ny, tmp, nx, d3.nsys * 3 * nz, 3 * nz, st, pl->tw, d3, s);
+    if (e == hipSuccess) e = launch_axis3(AX_GREEN, nz, tmp, nx * ny, d3.nsys, 1, st, pl->tw, d3, s, planes);
+    if (e == hipSuccess && ypass) e = launch_axis3(AX_INV, ny, tmp, nx, d3.nsys * 3 * nz, 3 * nz, st, pl->tw, d3, s);
     return e;
+}
+
+// The inverse x (row) transforms of the spectrum tmp with epilogue epi; with
+// the y transforms where the planes are one pass.
+hipError_t inverse_pass(fwils_plan pl, const ProbHost& P, const ProbDev& d, int epi, const cplx* tmp, const cplx* u,
+                        const cplx* aux, cplx* out, double* part, const SysState* st, hipStream_t s,
+                        const GmEpi* ge = nullptr) {
+    if (by_planes(P, epi)) {
+        const int pps = P.rps / P.ny;
+        return launch_plane(P.p.nx, P.ny, epi, tmp, out, u, aux, part, d.nsys * pps, pps, const_cast<SysState*>(st),
+                            pl->tw, s);
+    }
+    return launch_rows_inv(P.p.nx, P.cfg.row_pi, epi, tmp, u, aux, out, part, d.nsys * P.rps, P.rps, tile_rows(d), st,
+                           pl->tw, s, ge);
 }
 
 // The contrast stencil of either dimension (vector update vm, a.b the output).
@@ -250,14 +288,11 @@ hipError_t stencil_any(const ProbHost& P, const ProbDev& d, int vm, const Stenci
 
 // y = G0 conv f for problem P (f read, out written; tmp is scratch).
 hipError_t conv_problem(fwils_plan pl, const ProbHost& P, const cplx* f, cplx* out) {
-    const int rows = P.p.nsys * P.rps;
     cplx* tmp = at(pl->tmp, P);
-    hipError_t e = launch_rows_fwd(P.p.nx, P.cfg.row_p, f, tmp, rows, P.rps, tile_rows(P.dev), nullptr, pl->tw,
-                                   pl->stream);
-    if (e == hipSuccess) e = spectral(pl, P, P.dev, tmp, nullptr, pl->stream);
+    hipError_t e = forward_pass(pl, P, P.dev, EPI_STORE, f, tmp, nullptr, pl->stream);
+    if (e == hipSuccess) e = spectral(pl, P, P.dev, EPI_STORE, tmp, nullptr, pl->stream);
     if (e == hipSuccess)
-        e = launch_rows_inv(P.p.nx, P.cfg.row_pi, EPI_STORE, tmp, nullptr, nullptr, out, nullptr, rows,
-                            P.rps, tile_rows(P.dev), nullptr, pl->tw, pl->stream);
+        e = inverse_pass(pl, P, P.dev, EPI_STORE, tmp, nullptr, nullptr, out, nullptr, nullptr, pl->stream);
     return e;
 }
 
@@ -268,7 +303,6 @@ hipError_t conv_problem(fwils_plan pl, const ProbHost& P, const cplx* f, cplx* o
 hipError_t matvec(fwils_plan pl, const ProbHost& P, const ProbDev& d, const cplx* u, cplx* tmp,
                   const real* maps, int epi, const cplx* aux, cplx* out, double* part,
                   const SysState* st, hipStream_t s, const GmEpi* ge = nullptr, cplx* tmp2 = nullptr) {
-    const int rows = d.nsys * P.rps;
     const KernelCfg& k = P.cfg;
     hipError_t e = hipSuccess;
     if (k.fuse_p) {
@@ -278,12 +312,10 @@ hipError_t matvec(fwils_plan pl, const ProbHost& P, const ProbDev& d, const cplx
         if (!tmp2) tmp2 = pl->tmp2 + (tmp - pl->tmp);
         const StencilArgs a{u, nullptr, nullptr, nullptr, tmp2, maps, nullptr, 0};
         e = stencil_any(P, d, VM_NONE, a, const_cast<SysState*>(st), s);
-        if (e == hipSuccess) e = launch_rows_fwd(d.nx, k.row_p, tmp2, tmp, rows, P.rps, tile_rows(d), st, pl->tw, s);
+        if (e == hipSuccess) e = forward_pass(pl, P, d, epi, tmp2, tmp, st, s);
     }
-    if (e == hipSuccess) e = spectral(pl, P, d, tmp, st, s);
-    if (e == hipSuccess)
-        e = launch_rows_inv(d.nx, k.row_pi, epi, tmp, u, aux, out, part, rows, P.rps, tile_rows(d), st, pl->tw, s,
-                            ge);
+    if (e == hipSuccess) e = spectral(pl, P, d, epi, tmp, st, s);
+    if (e == hipSuccess) e = inverse_pass(pl, P, d, epi, tmp, u, aux, out, part, st, s, ge);
     return e;
 }
 
@@ -322,8 +354,6 @@ SysView make_view(fwils_plan pl, const ProbHost& P, int s0, int ns) {
 // alone (a timing aid; needs !first).
 hipError_t bicg_iteration(fwils_plan pl, const ProbHost& P, const SysView& V, int parity, bool first,
                           hipStream_t s, bool px_only = false) {
-    const int ns = V.d.nsys;
-    const int rows = ns * P.rps;
     cplx *x = pl->x + V.foff, *r = pl->r + V.foff, *rh = pl->rhat + V.foff, *v = pl->v + V.foff,
            *sv = pl->s + V.foff, *t = pl->t + V.foff, *tmp = pl->tmp + V.foff;
     cplx* pold = (parity ? pl->p2 : pl->p) + V.foff;
@@ -346,22 +376,17 @@ hipError_t bicg_iteration(fwils_plan pl, const ProbHost& P, const SysView& V, in
         StencilArgs a2 = a;   // the separate stencil writes tmp2, the rows read it
         a2.b = pl->tmp2 + V.foff;
         hipError_t r = stencil_any(P, V.d, vm, a2, st, s);
-        if (r == hipSuccess)
-            r = launch_rows_fwd(V.d.nx, k.row_p, a2.b, tmp, rows, P.rps, tile_rows(V.d), st, pl->tw, s);
+        if (r == hipSuccess) r = forward_pass(pl, P, V.d, EPI_BICG_V, a2.b, tmp, st, s);
         return r;
     };
     hipError_t e = stencil_rows(first ? VM_P : VM_PX, ap);
     if (px_only) return e;
-    if (e == hipSuccess) e = spectral(pl, P, V.d, tmp, st, s);
-    if (e == hipSuccess)
-        e = launch_rows_inv(V.d.nx, k.row_pi, EPI_BICG_V, tmp, pnew, rh, v, pV, rows, P.rps, tile_rows(V.d), st,
-                            pl->tw, s);
+    if (e == hipSuccess) e = spectral(pl, P, V.d, EPI_BICG_V, tmp, st, s);
+    if (e == hipSuccess) e = inverse_pass(pl, P, V.d, EPI_BICG_V, tmp, pnew, rh, v, pV, st, s);
     const StencilArgs as{r, v, nullptr, sv, tmp, maps, pV, P.np_rows};
     if (e == hipSuccess) e = stencil_rows(VM_S, as);
-    if (e == hipSuccess) e = spectral(pl, P, V.d, tmp, st, s);
-    if (e == hipSuccess)
-        e = launch_rows_inv(V.d.nx, k.row_pi, EPI_BICG_T, tmp, sv, rh, t, pT, rows, P.rps, tile_rows(V.d), st,
-                            pl->tw, s);
+    if (e == hipSuccess) e = spectral(pl, P, V.d, EPI_BICG_T, tmp, st, s);
+    if (e == hipSuccess) e = inverse_pass(pl, P, V.d, EPI_BICG_T, tmp, sv, rh, t, pT, st, s);
     return e;
 }
 
@@ -633,7 +658,7 @@ hipError_t gm_start(fwils_plan pl, const ProbHost& P, const cplx* b, double rtol
     const GmEpi ge{nullptr, 0, 0, a.part};
     hipError_t e = matvec(pl, P, P.dev, at(pl->x, P), at(pl->tmp, P), maps_at(pl, P), EPI_GMRES_R0,
                           b + P.field_off, a.V, nullptr, a.st, s, &ge);
-    if (e == hipSuccess) e = launch_gm_sum(a, GM_SUM_BEGIN, P.np_rows, 0, false, rtol, first, s);
+    if (e == hipSuccess) e = launch_gm_sum(a, GM_SUM_BEGIN, P.np_gm, 0, false, rtol, first, s);
     return e;
 }
 
@@ -654,7 +679,7 @@ hipError_t gm_cycle(fwils_plan pl, const ProbHost& P, const cplx* b, double rtol
         cplx* wn = a.V + (size_t)(j + 1) * a.vstride;
         e = matvec(pl, P, P.dev, wj, at(pl->tmp, P), maps_at(pl, P), EPI_ARNOLDI, nullptr, wn, nullptr, a.st, s,
                    &ge);
-        if (e == hipSuccess) e = launch_gm_sum(a, GM_SUM_PROJ1, P.np_rows, j, cgs2, rtol, false, s);
+        if (e == hipSuccess) e = launch_gm_sum(a, GM_SUM_PROJ1, P.np_gm, j, cgs2, rtol, false, s);
         if (e == hipSuccess) e = launch_gm_update(a, j, 1, !cgs2, s);
         if (cgs2) {
             if (e == hipSuccess) e = launch_gm_dots(a, j, s);
@@ -805,9 +830,11 @@ void layout_plan(fwils_plan pl) {
         P.data_off = 0;
         P.nrec = 0;
         P.tuned_us[0] = P.tuned_us[1] = P.tuned_us[2] = P.tuned_us[3] = 0.f;
-        P.np_rows = row_geom(P.p.nx, P.cfg.row_pi, P.rps).blocks_per_sys;   // the inverse pass's partials
+        P.np_gm = P.np_rows = row_geom(P.p.nx, P.cfg.row_pi, P.rps).blocks_per_sys;   // the inverse pass's partials
+        P.planes = P.d3 && plane_size_ok(P.p.nx, P.ny);
+        if (P.planes) P.np_rows = P.rps / P.ny / plane_geom(P.p.nx, P.ny, P.rps / P.ny).G;
         P.np_vec = vec_blocks_per_sys((int)P.n_per_sys);
-        pl->max_np = std::max(pl->max_np, P.np_vec);
+        pl->max_np = std::max({pl->max_np, P.np_vec, P.np_rows});
         {   // partial buffers fit every row-transform variant
             int cand[3];
             const int nc = row_candidates(P.p.nx, cand);
@@ -1881,19 +1908,20 @@ fwils_status fwils_apply_pass(fwils_plan plan, int32_t pass, const void* u, void
     for (const ProbHost& P : plan->probs) {
         const int rows = P.p.nsys * P.rps;
         cplx* tmp = at(plan->tmp, P);
-        if (P.d3) {   // stencil / x rows / y, z (Green) and y transforms / inverse x rows
+        // 3-D: the stencil / x transforms / y, z (Green) and y transforms /
+        // inverse x transforms, the y transforms with the x transforms where
+        // the planes are one pass
+        if (P.d3) {
             if (pass == 0) {
                 const StencilArgs a{at(u, P), nullptr, nullptr, nullptr, at(plan->tmp2, P), maps_at(plan, P), nullptr, 0};
                 FW_HIP(stencil_any(P, P.dev, VM_NONE, a, nullptr, s));
             } else if (pass == 1) {
-                FW_HIP(launch_rows_fwd(P.p.nx, P.cfg.row_p, at(plan->tmp2, P), tmp, rows, P.rps, SpecLayout{}, nullptr,
-                                       plan->tw, s));
+                FW_HIP(forward_pass(plan, P, P.dev, EPI_APPLY, at(plan->tmp2, P), tmp, nullptr, s));
             } else if (pass == 2) {
-                FW_HIP(spectral(plan, P, P.dev, tmp, nullptr, s));
+                FW_HIP(spectral(plan, P, P.dev, EPI_APPLY, tmp, nullptr, s));
             } else {
-                FW_HIP(launch_rows_inv(P.p.nx, P.cfg.row_pi, EPI_APPLY, tmp, at(u, P), nullptr,
-                                       static_cast<cplx*>(Au) + P.field_off, nullptr, rows, P.rps, SpecLayout{}, nullptr,
-                                       plan->tw, s));
+                FW_HIP(inverse_pass(plan, P, P.dev, EPI_APPLY, tmp, at(u, P), nullptr,
+                                    static_cast<cplx*>(Au) + P.field_off, nullptr, nullptr, s));
             }
             continue;
         }
@@ -2261,7 +2289,7 @@ bool cfg_ok(const ProbHost& P, const KernelCfg& k) {
 void apply_cfg(fwils_plan pl, ProbHost& P, const KernelCfg& k) {
     P.cfg = k;
     P.dev.tile_sh = col_tile_shift(P.p.nx, k.col.W);   // the spectrum follows the column blocks
-    P.np_rows = row_geom(P.p.nx, k.row_pi, 2 * P.p.nz).blocks_per_sys;
+    P.np_gm = P.np_rows = row_geom(P.p.nx, k.row_pi, 2 * P.p.nz).blocks_per_sys;
     drop_graphs(pl);
 }
 

@@ -304,6 +304,7 @@ __device__ __forceinline__ void dft(cplx (&x)[R]) {
     else if constexpr (R == 5) dft5<INV>(x[0], x[1], x[2], x[3], x[4]);
     else if constexpr (R == 4) dft4<INV>(x[0], x[1], x[2], x[3]);
     else if constexpr (R == 8) dft8<INV>(x);
+    else if constexpr (R == 6) dft_pfa<2, 3, INV>(x);
     else if constexpr (R == 10) dft_pfa<2, 5, INV>(x);
     else if constexpr (R == 12) dft_pfa<4, 3, INV>(x);
     else if constexpr (R == 20) dft_pfa<4, 5, INV>(x);

@@ -673,7 +673,7 @@ __device__ __forceinline__ real axis_k(int i, int n, real dk, real dx, bool cent
 template <int N, int P, int MODE>
 __global__ __launch_bounds__(256) void k_axis(cplx* __restrict__ data, int S, int W, int slabs_per_sys,
                                               const SysState* __restrict__ st, const cplx* __restrict__ tw,
-                                              ProbDev3 pd) {
+                                              ProbDev3 pd, PlaneOrder ord) {
     using FS = FftShape<N, P>;
     constexpr int T = FS::T;
     constexpr int PL = PaddedLen<N>::value;
@@ -701,7 +701,12 @@ __global__ __launch_bounds__(256) void k_axis(cplx* __restrict__ data, int S, in
     const int tt = active ? t : 0;
     if constexpr (MODE != AX_INV) fft_run<N, P, false, NC>(v, tt, tw, lds);
     if constexpr (MODE == AX_GREEN) {
-        const int ix = col % pd.nx, iy = col / pd.nx;
+        int ix = col % pd.nx, iy = col / pd.nx;
+        if (ord.planes) {   // column y + ny x of the positions R2 k1 + k2
+            const int px = col / pd.ny, py = col - px * pd.ny;
+            ix = px / ord.x2 + ord.x1 * (px % ord.x2);
+            iy = py / ord.y2 + ord.y1 * (py % ord.y2);
+        }
         const bool central = pd.symbol == 1;
         const real kx = axis_k(ix, pd.nx, pd.dk[0], pd.dx, central);
         const real ky = axis_k(iy, pd.ny, pd.dk[1], pd.dx, central);
@@ -756,7 +761,7 @@ bool axis3_size_supported(int n) {
 
 template <int N, int MODE>
 static hipError_t axis_launch(cplx* data, int S, int nslab, int slabs_per_sys, const SysState* st, const cplx* tw,
-                              const ProbDev3& pd, hipStream_t s) {
+                              const ProbDev3& pd, hipStream_t s, const PlaneOrder& ord = PlaneOrder{}) {
     constexpr int P = (N % 5 == 0) ? 10 : (N % 3 == 0) ? 12 : 8;
     constexpr int T = N / P;
     constexpr int NC = MODE == AX_GREEN ? 3 : 1;
@@ -769,21 +774,72 @@ static hipError_t axis_launch(cplx* data, int S, int nslab, int slabs_per_sys, c
     const long long blocks = (long long)nslab * (S / W);
     if (blocks > 0x7fffffffLL) return hipErrorInvalidValue;
     hipLaunchKernelGGL((k_axis<N, P, MODE>), dim3((unsigned)blocks), dim3(threads), lds, s, data, S, W,
-                       slabs_per_sys, st, tw + twiddle_offset(N), pd);
+                       slabs_per_sys, st, tw + twiddle_offset(N), pd, ord);
     return hipGetLastError();
 }
 
 hipError_t launch_axis3(int mode, int n, cplx* data, int S, int nslab, int slabs_per_sys, const SysState* st,
-                        const cplx* tw, const ProbDev3& pd, hipStream_t s) {
+                        const cplx* tw, const ProbDev3& pd, hipStream_t s, bool planes) {
+    PlaneOrder ord{};
+    if (planes) {
+        if (!plane_size_ok(pd.nx, pd.ny)) return hipErrorInvalidValue;
+        ord = PlaneOrder{1, plane_radix(pd.nx), pd.nx / plane_radix(pd.nx), plane_radix(pd.ny),
+                         pd.ny / plane_radix(pd.ny)};
+    }
 #define FW_AX(N)                                                                                             \
     if (n == N) {                                                                                            \
         if (mode == AX_FWD) return axis_launch<N, AX_FWD>(data, S, nslab, slabs_per_sys, st, tw, pd, s);     \
         if (mode == AX_INV) return axis_launch<N, AX_INV>(data, S, nslab, slabs_per_sys, st, tw, pd, s);     \
-        if (mode == AX_GREEN) return axis_launch<N, AX_GREEN>(data, S, nslab, slabs_per_sys, st, tw, pd, s); \
+        if (mode == AX_GREEN) return axis_launch<N, AX_GREEN>(data, S, nslab, slabs_per_sys, st, tw, pd, s, ord); \
     }
     FW_AXIS_SIZES(FW_AX)
 #undef FW_AX
     return hipErrorInvalidValue;
+}
+
+// -------------------------------------------------------- x-y planes -----
+// Planes per block: whole planes until the block has about 256 threads' work
+// (a butterfly each) in its widest sweep.  Threads: up to 512, since a sweep's
+// items rarely divide evenly (80 x 40 x 32 x 100, forward: 95 us by 512
+// threads, 98 by 256, 320 or 384).  The inverse pass holds 118 registers, 16
+// wavefronts per CU: blocks of four wavefronts where four of them fit in LDS
+// (140 -> 135 us there; 48 x 48 x 64 x 9: 20.1 -> 17.6 us), else of eight
+// (96 x 64 x 48 x 7: 24.2 us against 27.5 by four); five or six wavefronts
+// leave a quarter of them unused (157 us).
+PlaneGeom plane_geom(int nx, int ny, int planes_per_sys) {
+    const int x1 = plane_radix(nx), y1 = plane_radix(ny);
+    const int items = nx * ny / std::min(std::min(x1, nx / x1), std::min(y1, ny / y1));
+    const size_t lds = (size_t)ny * (nx + 1) * sizeof(cplx);
+    PlaneGeom g;
+    g.G = std::max(1, std::min(256 / items, (int)(kPlaneLds / lds)));
+    while (planes_per_sys % g.G != 0) --g.G;
+    g.threads = std::min(512, ((g.G * items + 63) / 64) * 64);
+    g.lds = g.G * lds;
+    g.threads_inv = 4 * (g.lds + 1024) <= kMaxLds ? std::min(256, g.threads) : g.threads;
+    return g;
+}
+
+hipError_t launch_plane_a(int, int, int, const PlaneGeom&, const cplx*, cplx*, const cplx*, const cplx*, double*, int,
+                          int, SysState*, const cplx*, hipStream_t);
+hipError_t launch_plane_b(int, int, int, const PlaneGeom&, const cplx*, cplx*, const cplx*, const cplx*, double*, int,
+                          int, SysState*, const cplx*, hipStream_t);
+hipError_t launch_plane_c(int, int, int, const PlaneGeom&, const cplx*, cplx*, const cplx*, const cplx*, double*, int,
+                          int, SysState*, const cplx*, hipStream_t);
+
+hipError_t launch_plane(int nx, int ny, int epi, const cplx* in, cplx* out, const cplx* u, const cplx* aux,
+                        double* part, int nplanes, int planes_per_sys, SysState* st, const cplx* tw, hipStream_t s) {
+    const bool rec = epi == EPI_BICG_V || epi == EPI_BICG_T || epi == EPI_TRUERES;
+    if (!plane_size_ok(nx, ny) || nplanes < 1 || planes_per_sys < 1 || nplanes % planes_per_sys != 0 ||
+        !(epi == PLANE_FWD || epi == EPI_STORE || epi == EPI_APPLY || rec) || !in || !out || in == out ||
+        (epi >= EPI_APPLY && !u) || (rec && (!aux || !part)) || (epi == EPI_BICG_T && !st))
+        return hipErrorInvalidValue;
+    const PlaneGeom g = plane_geom(nx, ny, planes_per_sys);
+    hipError_t e = launch_plane_a(nx, ny, epi, g, in, out, u, aux, part, nplanes, planes_per_sys, st, tw, s);
+    if (e == hipErrorInvalidValue)
+        e = launch_plane_b(nx, ny, epi, g, in, out, u, aux, part, nplanes, planes_per_sys, st, tw, s);
+    if (e == hipErrorInvalidValue)
+        e = launch_plane_c(nx, ny, epi, g, in, out, u, aux, part, nplanes, planes_per_sys, st, tw, s);
+    return e;
 }
 
 // ---------------------------------------------------- sources, receivers --

@@ -191,8 +191,47 @@ hipError_t launch_stencil3(int vm, const StencilArgs& a, const ProbDev3& pd, Sys
 // Strided-axis transforms in place: [nslab][n][S] (AX_FWD / AX_INV; system of
 // a slab = slab / slabs_per_sys) or [nsys][3][n][S] (AX_GREEN, nslab = nsys,
 // the z pass with the 3 x 3 Green multiply and the 1 / (nx ny nz) scale).
+// AX_GREEN takes the spectrum's columns in plane order where `planes` is set.
 hipError_t launch_axis3(int mode, int n, cplx* data, int S, int nslab, int slabs_per_sys, const SysState* st,
-                        const cplx* tw, const ProbDev3& pd, hipStream_t s);
+                        const cplx* tw, const ProbDev3& pd, hipStream_t s, bool planes = false);
+// The x and y transforms of whole [ny][nx] planes in one pass
+// (plane_kernels.h; complex64): forward (epi = PLANE_FWD) or inverse with one
+// of the epilogues EPI_STORE, EPI_APPLY, EPI_BICG_V, EPI_BICG_T, EPI_TRUERES
+// (the GMRES epilogues keep the separate passes).
+constexpr int PLANE_FWD = -1;
+// First radix R1 of an axis of n = R1 R2 points; at most 8 up to 128 points
+// (the epilogue of the inverse pass holds three values per point of it).
+constexpr int plane_radix(int n) {
+    return n == 16 || n == 20 ? 4 : n == 160 ? 10 : n == 192 ? 12 : n == 256 ? 16 : 8;
+}
+// Sizes with a plane kernel: every plane that fits in LDS beside the block
+// sums, also where a CU then holds one block only (128 x 128 x 64 x 4, the
+// matvec: 240 us by planes, 290 us by separate passes; 64^3 x 32: 429 against
+// 692 us; 80 x 40 x 32 x 100: 550 against 690 us).
+constexpr size_t kPlaneLds = kMaxLds - 1024;
+constexpr bool plane_size_ok(int nx, int ny) {
+#ifdef FW_C128
+    return false;
+#else
+    return nx >= 16 && ny >= 16 && (size_t)ny * (nx + 1) * sizeof(cplx) <= kPlaneLds;
+#endif
+}
+// Order of a 3-D spectrum's [nx ny] columns between the passes.  Row-major:
+// column ix + nx iy.  Planes: column y + ny x of the positions x = R2 k1 + k2
+// (k = k1 + R1 k2) the plane passes leave.
+struct PlaneOrder {
+    int planes;        // 0: row-major
+    int x1, x2, y1, y2;
+};
+struct PlaneGeom {
+    int G;             // planes per block
+    int threads;       // of the forward pass
+    int threads_inv;   // of the inverse pass
+    size_t lds;
+};
+PlaneGeom plane_geom(int nx, int ny, int planes_per_sys);
+hipError_t launch_plane(int nx, int ny, int epi, const cplx* in, cplx* out, const cplx* u, const cplx* aux,
+                        double* part, int nplanes, int planes_per_sys, SysState* st, const cplx* tw, hipStream_t s);
 hipError_t launch_point_sources3(cplx* f, const int32_t* src_ixyz, const double* src_f, const ProbDev3& pd,
                                  hipStream_t s);
 hipError_t launch_gather3(const cplx* w, cplx* d, const int32_t* rec, int nrec, const ProbDev3& pd, hipStream_t s);

@@ -97,6 +97,30 @@ def test_marching_stencil_column_shapes(nx, ny, nz):
     assert _rel(_np(plan.view(plan.body_force(ut), 0)), P.body_force(u)) < KERNEL_TOL
 
 
+@pytest.mark.parametrize("nx,ny,nz,nsys", [
+    (16, 16, 20, 3),     # several planes per block, the smallest radices
+    (20, 24, 16, 1), (24, 20, 32, 2), (32, 160, 16, 1), (48, 32, 24, 2), (256, 16, 16, 1), (16, 256, 16, 1),
+    (192, 40, 16, 1),
+    (96, 80, 16, 2),     # one block above the default LDS limit per block
+    (128, 128, 16, 1),   # one block per CU
+    (160, 160, 16, 1),   # planes too large for LDS: separate x and y passes
+])
+def test_plane_transforms(nx, ny, nz, nsys):
+    """The x-y plane passes: convolution (plain store) and operator (epilogue)
+    against the oracle, and a solve's own records through its true residual.
+    Single-precision transforms of N points err by a few 1e-7 sqrt(log2 N)."""
+    print(f"planes {nx}x{ny}x{nz} x {nsys}", flush=True)
+    plan, p, maps, P = _case(nx, ny, nz, nsys)
+    u = _field(np.random.default_rng(6), nsys, nx, ny, nz)
+    ut = plan.pack([u])
+    assert _rel(_np(plan.view(plan.convolve(ut), 0)), P.convolve(u)) < KERNEL_TOL
+    assert _rel(_np(plan.view(plan.apply(ut), 0)), P.apply(u)) < KERNEL_TOL
+    res = plan.solve(ut, rtol=1e-5, maxit=400)
+    assert res.status == 0 and np.all(res.relres <= 2e-5), (res.status, res.relres)
+    x = _np(plan.view(res.x, 0))
+    assert _rel(P.apply(x), u) < 2e-5 + KERNEL_TOL
+
+
 @pytest.mark.parametrize("params", ["vti", "general"])
 def test_solve_3d_matches_oracle_batched_plain_gmres(params):
     nx, ny, nz = 24, 20, 16
