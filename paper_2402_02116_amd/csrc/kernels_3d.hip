@@ -14,6 +14,7 @@
 // The x transforms are the row kernels of the 2-D path (rows of nx points).
 #include <algorithm>
 #include <numeric>
+#include <type_traits>
 
 #include "bicg.h"
 #include "fft_kernels.h"
@@ -263,66 +264,88 @@ __global__ __launch_bounds__(256) void k_stencil3(const cplx* __restrict__ u, co
 
 // The same stencil (plain: b of the input u) marching along z: a block owns
 // a TX x TY column of cells over the z range [z0, z1) of one system and walks
-// it plane by plane.  Each thread owns one cell of the column (p0) and, for
-// the first RING threads, one cell of the 2-cell xy halo ring around it (p1),
-// and keeps the input of planes z, z+1, z+2 at those cells in registers.  LDS
-// holds only plane z+1 of the input (for the x and y differences) and the
-// stress s' of plane z with a 1-cell halo.  Step z: the stress of plane z+1
-// at the own and inner ring cells (z differences from registers), then b on
-// plane z (the z difference of the own column's stress from registers), then
-// plane z+2 and the new stress replace the LDS planes; the next two planes
-// are loads in flight meanwhile.  Every input plane of the range is read
-// once, plus three halo planes and the own column of a fourth per range.
+// it plane by plane.  FULL: TX = nx, so that the column has halo rows only (a
+// narrower one fetches a whole cache line for every two cells of its halo
+// columns: with 16 x 16 columns at 80 x 40 the L1 fetched nine times the
+// field from L2 and the pass waited on it; the halo columns in LDS are the
+// row's own other end).  Each thread owns one cell of the column, and the
+// first NH threads (in the rotated numbering below) also one cell of the
+// halo: the NR cells next to the column, where the stress is needed too, then
+// those at distance two (and the corners between them).
+// LDS holds the input planes z+1 (for the x and y differences) and z (each
+// thread's own cells), and the stress s' of plane z (all but s'_zz, which only
+// the own z difference takes) and of z+1 as it is made.  Step z takes the
+// input of plane z+2 at the thread's cells from registers, forms the stress of
+// plane z+1 at the own and halo cells, then b on plane z, and puts plane z+2 in
+// the place of plane z: one barrier per step.  The loop is unrolled by two, the
+// period in which registers and LDS copies change roles, so that nothing is
+// moved between registers; the next plane and its maps are in flight
+// meanwhile.  Every input plane of the range is read once, plus three halo
+// planes and the own column of a fourth.
 // The BiCGSTAB update modes run as a streaming pass before it
 // (launch_bicg_update): fused into this kernel they held one or two waves
 // per SIMD.
-template <int TX, int TY>
+template <int TX, int TY, bool FULL>
 struct March3 {
     static constexpr int HX = TX + 4, HY = TY + 4, HP = HX * HY;   // input plane with halo 2
     static constexpr int SX = TX + 2, SY = TY + 2, SP = SX * SY;   // stress plane with halo 1
     static constexpr int NT = TX * TY;                             // one thread per own cell
-    static constexpr int RING = HP - NT;                           // halo cells of an input plane
+    static constexpr int NR = FULL ? 2 * TX : 2 * (TX + TY);       // halo cells next to the column
+    static constexpr int NH = FULL ? 4 * TX : 2 * NR + 4;          // halo cells of an input plane
+    static constexpr int NL = 5;                                   // stress components in LDS
+    // Copies of the stress planes: with one, a step waits a second time, for
+    // the stress of plane z to be read before that of z+1 replaces it, but 1.4
+    // times as many blocks fit in LDS (64^3 x 32: 133 -> 127 us, 128 x 128 x 64
+    // x 4: 74 -> 65 us).  A block of five wavefronts puts two on one SIMD, so
+    // that the registers allow two blocks at most, which fit with two copies
+    // (80 x 40 x 32 x 100: 180 us, 187 with one).
+    static constexpr int NB = NT / 64 == 5 ? 2 : 1;
 };
 
-template <int TX, int TY>
+template <int TX, int TY, bool FULL>
 inline size_t march3_lds() {
-    using M = March3<TX, TY>;
-    return (size_t)(3 * M::HP + 6 * M::SP) * sizeof(cplx);
+    using M = March3<TX, TY, FULL>;
+    return (size_t)(2 * 3 * M::HP + M::NB * M::NL * M::SP) * sizeof(cplx);
 }
 
-// Halo-ring cell k of a (TX+4) x (TY+4) plane: the two rows above, the two
-// rows below, then the two columns left and right of the own rows.
-template <int TX, int TY>
-__device__ __forceinline__ void ring_cell(int k, int& hx, int& hy) {
-    constexpr int HX = TX + 4;
-    if (k < 2 * HX) {
-        hy = k / HX;
-        hx = k % HX;
-    } else if (k < 4 * HX) {
-        k -= 2 * HX;
-        hy = TY + 2 + k / HX;
-        hx = k % HX;
-    } else if (k < 4 * HX + 2 * TY) {
-        k -= 4 * HX;
-        hy = 2 + k / 2;
-        hx = k % 2;
+// Halo cell k of the column, relative to its first cell: those at distance 1,
+// then 2 (rows above and below, and unless FULL columns left and right), then
+// the corners between them.
+template <int TX, int TY, bool FULL>
+__device__ __forceinline__ void halo_cell(int k, int& x, int& y) {
+    constexpr int NR = March3<TX, TY, FULL>::NR;
+    if (!FULL && k >= 2 * NR) {
+        x = (k & 1) ? TX : -1;
+        y = (k & 2) ? TY : -1;
+        return;
+    }
+    const int d = k < NR ? 1 : 2;
+    k -= (d - 1) * NR;
+    if (k < TX) {
+        x = k;
+        y = -d;
+    } else if (FULL || k < 2 * TX) {
+        x = k - TX;
+        y = TY - 1 + d;
+    } else if (k < 2 * TX + TY) {
+        x = -d;
+        y = k - 2 * TX;
     } else {
-        k -= 4 * HX + 2 * TY;
-        hy = 2 + k / 2;
-        hx = TX + 2 + k % 2;
+        x = TX - 1 + d;
+        y = k - 2 * TX - TY;
     }
 }
 
-template <bool GEN, int TX, int TY>
-__global__ __launch_bounds__(TX * TY) void k_stencil3z(const cplx* __restrict__ u, cplx* __restrict__ b,
+template <bool GEN, int TX, int TY, bool FULL>
+__global__ __launch_bounds__(TX * TY, sizeof(real) == 8 ? 1 : GEN ? 3 : 4) void k_stencil3z(const cplx* __restrict__ u, cplx* __restrict__ b,
                                                        const real* __restrict__ maps, ProbDev3 pd, int ZC,
                                                        const SysState* __restrict__ st) {
-    using M = March3<TX, TY>;
-    static_assert(M::RING <= M::NT, "one halo-ring cell per thread at most");
+    using M = March3<TX, TY, FULL>;
+    static_assert(M::NH <= M::NT && M::NT % 64 == 0, "one halo cell per thread at most");
     constexpr int NS = Params3<GEN>::NS;
     extern __shared__ __align__(16) unsigned char lds3[];
-    cplx* sp = reinterpret_cast<cplx*>(lds3);   // input plane [3][HP]
-    cplx* ss = sp + 3 * M::HP;                  // stress plane [6][SP]
+    cplx* const sp = reinterpret_cast<cplx*>(lds3);   // input plane [2][3][HP]
+    cplx* const ss = sp + 2 * 3 * M::HP;              // stress plane [2][NL][SP]: xx, yy, yz, xz, xy
     __shared__ int s_status;
 
     const int nx = pd.nx, ny = pd.ny, nz = pd.nz;
@@ -346,218 +369,248 @@ __global__ __launch_bounds__(TX * TY) void k_stencil3z(const cplx* __restrict__ 
         __syncthreads();
         if (s_status != ST_RUNNING) return;
     }
-    // this system's vectors; offsets within a system fit 32 bits (3 x 256^3)
-    const size_t so = (size_t)sys * 3 * cells;
-    const cplx* __restrict__ us = u + so;
-    cplx* __restrict__ bs = b + so;
-    const uint32_t cells32 = (uint32_t)cells, plane32 = (uint32_t)nx * (uint32_t)ny;
-    // planes z0-2 .. z1+3 lie within one period of the axis
-    auto zoff = [&](int z) -> uint32_t { return (uint32_t)(z < 0 ? z + nz : (z >= nz ? z - nz : z)) * plane32; };
+    // this system's vectors: uniform plane addresses and 32-bit offsets of the
+    // thread's cells within a plane
+    const cplx* __restrict__ us = u + (size_t)sys * 3 * cells;
+    cplx* __restrict__ bs = b + (size_t)sys * 3 * cells;
+    const uint32_t plane = (uint32_t)nx * (uint32_t)ny;
+    // planes z0-2 .. z1+1 lie within one period of the axis
+    auto zoff = [&](int z) -> size_t { return (size_t)((uint32_t)(z < 0 ? z + nz : (z >= nz ? z - nz : z)) * plane); };
     const uint32_t xy0 = (uint32_t)wrapm(y0 + ty, ny) * nx + wrapm(x0 + tx, nx);
 
-    // the thread's halo-ring cell
-    const bool has1 = t < M::RING;
-    int hx1 = 2, hy1 = 2;
-    if (has1) ring_cell<TX, TY>(t, hx1, hy1);
-    const bool st1 = has1 && hx1 >= 1 && hx1 <= TX + 2 && hy1 >= 1 && hy1 <= TY + 2;   // inner ring: stress
-    const uint32_t xy1 = (uint32_t)wrapm(y0 - 2 + hy1, ny) * nx + wrapm(x0 - 2 + hx1, nx);
-    const int h0 = (ty + 2) * M::HX + tx + 2, h1 = hy1 * M::HX + hx1;
-    const int q0 = (ty + 1) * M::SX + tx + 1, q1 = (hy1 - 1) * M::SX + hx1 - 1;
+    // the thread's halo cell; the wavefront with the extra stress differs from
+    // block to block, so that these wavefronts spread over the SIMDs
+    const int rt = ((t >> 6) + blk) % (M::NT / 64) * 64 + (t & 63);
+    const bool has1 = rt < M::NH, st1 = rt < M::NR;
+    int hx1 = 0, hy1 = 0;
+    if (has1) halo_cell<TX, TY, FULL>(rt, hx1, hy1);
+    // Every load of the march is unconditional, so that the compiler counts
+    // the loads in flight exactly and waits for one step's while the next
+    // step's travel (a load under a branch made every step wait for its own
+    // prefetch): threads without a halo cell load their own cell again.
+    const uint32_t xy1 = has1 ? (uint32_t)wrapm(y0 + hy1, ny) * nx + wrapm(x0 + hx1, nx) : xy0;
+    const uint32_t xys = st1 ? xy1 : xy0;
+    const int h0 = (ty + 2) * M::HX + tx + 2, h1 = (hy1 + 2) * M::HX + hx1 + 2;
+    const int q0 = (ty + 1) * M::SX + tx + 1, q1 = (hy1 + 1) * M::SX + hx1 + 1;
 
-    using Raw = cplx[3];
-    auto load_raw = [&](Raw& r, uint32_t g) {
-#pragma unroll
-        for (int c = 0; c < 3; ++c) r[c] = us[c * cells32 + g];
+    struct Cells {   // one plane of the input at the own and the halo cell
+        cplx o[3], h[3];
     };
-    auto convert = [&](const Raw& r, cplx (&f)[3]) {
+    auto load_own = [&](cplx (&r)[3], int z) {
+        const cplx* p = us + zoff(z);
 #pragma unroll
-        for (int c = 0; c < 3; ++c) f[c] = r[c];
+        for (int c = 0; c < 3; ++c) r[c] = (p + c * cells)[xy0];
     };
-    auto load_maps = [&](real (&m)[NS], uint32_t g) {
+    auto load_cells = [&](Cells& r, int z) {
+        load_own(r.o, z);
+        const cplx* p = us + zoff(z);
 #pragma unroll
-        for (int p = 0; p < NS; ++p) m[p] = maps[p * cells32 + g];
+        for (int c = 0; c < 3; ++c) r.h[c] = (p + c * cells)[xy1];
     };
-    // s' = dC e' at LDS input position h of the current plane; z differences
-    // from the planes below (lo) and above (hi)
-    auto stress_at = [&](int h, const cplx (&lo)[3], const cplx (&hi)[3], const real (&m)[NS], cplx (&sg)[6]) {
+    auto load_maps = [&](real (&m)[NS], int z, uint32_t xy) {
+        const real* p = maps + zoff(z);
+#pragma unroll
+        for (int q = 0; q < NS; ++q) m[q] = (p + q * cells)[xy];
+    };
+    const real* rho = maps + (size_t)NS * cells;
+    // s' = dC e' at position h of the LDS input plane w; z differences from
+    // the planes below (lo) and above (hi)
+    auto stress_at = [&](const cplx* w, const cplx (&lo)[3], const cplx (&hi)[3], const real (&m)[NS],
+                         cplx (&sg)[6]) {
         cplx d[3][3];
 #pragma unroll
         for (int c = 0; c < 3; ++c) {
-            const cplx* w = sp + c * M::HP + h;
-            d[c][0] = csub(w[1], w[-1]);
-            d[c][1] = csub(w[M::HX], w[-M::HX]);
+            d[c][0] = csub(w[c * M::HP + 1], w[c * M::HP - 1]);
+            d[c][1] = csub(w[c * M::HP + M::HX], w[c * M::HP - M::HX]);
             d[c][2] = csub(hi[c], lo[c]);
         }
         const cplx e[6] = {d[0][0], d[1][1], d[2][2], cadd(d[1][2], d[2][1]), cadd(d[0][2], d[2][0]),
                            cadd(d[0][1], d[1][0])};
         stress3<GEN>(m, 1, e, sg);
     };
-    auto put_plane = [&](const cplx (&f0)[3], const cplx (&f1)[3]) {
+    // FULL: a row's two end cells are also the halo cells of its other end
+    const bool end0 = FULL && (tx < 2 || tx >= TX - 2), end1 = FULL && (hx1 < 2 || hx1 >= TX - 2);
+    const int o0 = tx < 2 ? TX : -TX, o1 = hx1 < 2 ? TX : -TX;
+    auto put_plane = [&](int k, const Cells& f) {
+        cplx* w = sp + k * 3 * M::HP;
 #pragma unroll
-        for (int c = 0; c < 3; ++c) {
-            sp[c * M::HP + h0] = f0[c];
-            if (has1) sp[c * M::HP + h1] = f1[c];
+        for (int c = 0; c < 3; ++c) w[c * M::HP + h0] = f.o[c];
+        if (end0) {
+#pragma unroll
+            for (int c = 0; c < 3; ++c) w[c * M::HP + h0 + o0] = f.o[c];
+        }
+        if (has1) {
+#pragma unroll
+            for (int c = 0; c < 3; ++c) w[c * M::HP + h1] = f.h[c];
+            if (end1) {
+#pragma unroll
+                for (int c = 0; c < 3; ++c) w[c * M::HP + h1 + o1] = f.h[c];
+            }
         }
     };
-
-    // ---- prologue: planes z0-2 (own column), z0-1, z0, z0+1, z0+2
-    cplx fa0[3], fa1[3], fb0[3], fb1[3], fc0[3], fc1[3];
-    cplx sold[6];
-    {
-        Raw r0, r1;
-        cplx fm2[3], fm0[3], fm1[3];
-        load_raw(r0, zoff(z0 - 2) + xy0);
-        convert(r0, fm2);
-        load_raw(r0, zoff(z0 - 1) + xy0);
-        convert(r0, fm0);
-        if (has1) {
-            load_raw(r1, zoff(z0 - 1) + xy1);
-            convert(r1, fm1);
-        }
-        load_raw(r0, zoff(z0) + xy0);
-        convert(r0, fa0);
-        if (has1) {
-            load_raw(r1, zoff(z0) + xy1);
-            convert(r1, fa1);
-        }
-        put_plane(fm0, fm1);
-        real m[NS];
-        load_maps(m, zoff(z0 - 1) + xy0);
-        __syncthreads();
-        stress_at(h0, fm2, fa0, m, sold);   // own stress of plane z0-1
-        load_raw(r0, zoff(z0 + 1) + xy0);
-        convert(r0, fb0);
-        if (has1) {
-            load_raw(r1, zoff(z0 + 1) + xy1);
-            convert(r1, fb1);
-        }
-        __syncthreads();
-        put_plane(fa0, fa1);
-        __syncthreads();
-        cplx sg[6];
-        load_maps(m, zoff(z0) + xy0);
-        stress_at(h0, fm0, fb0, m, sg);   // stress of plane z0
-#pragma unroll
-        for (int i = 0; i < 6; ++i) ss[i * M::SP + q0] = sg[i];
-        if (st1) {
-            load_maps(m, zoff(z0) + xy1);
-            stress_at(h1, fm1, fb1, m, sg);
-#pragma unroll
-            for (int i = 0; i < 6; ++i) ss[i * M::SP + q1] = sg[i];
-        }
-        load_raw(r0, zoff(z0 + 2) + xy0);
-        convert(r0, fc0);
-        if (has1) {
-            load_raw(r1, zoff(z0 + 2) + xy1);
-            convert(r1, fc1);
-        }
-        __syncthreads();
-        put_plane(fb0, fb1);
-    }
-    // in flight during a step: planes z+3 and z+4 (two buffers, used in
-    // turn: the loop is unrolled by two so that no register of a load in
-    // flight is moved) and the maps of plane z+2
-    Raw rA0, rA1, rB0, rB1;
-    load_raw(rA0, zoff(z0 + 3) + xy0);
-    if (has1) load_raw(rA1, zoff(z0 + 3) + xy1);
-    load_raw(rB0, zoff(z0 + 4) + xy0);
-    if (has1) load_raw(rB1, zoff(z0 + 4) + xy1);
-    // stiffness maps of plane z+1 (and, prefetched, z+2); the 21-constant
+    auto put_stress = [&](int k, int q, const cplx (&s)[6]) {
+        cplx* w = ss + (M::NB == 2 ? k : 0) * M::NL * M::SP + q;
+        w[0] = s[0];
+        w[M::SP] = s[1];
+        w[2 * M::SP] = s[3];
+        w[3 * M::SP] = s[4];
+        w[4 * M::SP] = s[5];
+    };
+    auto put_own_stress = [&](int k, const cplx (&s)[6]) {
+        put_stress(k, q0, s);
+        if (FULL && (tx == 0 || tx == TX - 1)) put_stress(k, q0 + o0, s);
+    };
+    struct ZStress {   // the own stress components whose z difference is taken
+        cplx zz, yz, xz;
+    };
+    // the maps of the next stress plane, loaded a step ahead; the 21-constant
     // form loads them at the step instead (registers)
-    constexpr int NPF = GEN ? 1 : NS;
-    real mc0[NS], mc1[NS], mn0[NPF], mn1[NPF];
-    if constexpr (!GEN) {
-        load_maps(mc0, zoff(z0 + 1) + xy0);
-        if (st1) load_maps(mc1, zoff(z0 + 1) + xy1);
-        load_maps(mn0, zoff(z0 + 2) + xy0);
-        if (st1) load_maps(mn1, zoff(z0 + 2) + xy1);
+    constexpr int NM = GEN ? 1 : NS;
+    struct Maps {
+        real o[NM], h[NM], rho;
+    };
+    auto load_step_maps = [&](Maps& m, int z) {   // stress of plane z + 1, density of plane z
+        if constexpr (!GEN) {
+            load_maps(m.o, z + 1, xy0);
+            load_maps(m.h, z + 1, xys);
+        }
+        m.rho = (rho + zoff(z))[xy0];
+    };
+
+    // the thread's cells of LDS input plane k
+    auto get_own = [&](cplx (&r)[3], int k) {
+#pragma unroll
+        for (int c = 0; c < 3; ++c) r[c] = sp[(k * 3 + c) * M::HP + h0];
+    };
+    auto get_halo = [&](cplx (&r)[3], int k) {
+#pragma unroll
+        for (int c = 0; c < 3; ++c) r[c] = sp[(k * 3 + c) * M::HP + h1];
+    };
+
+    // ---- prologue: stress of plane z0-1 (own) and z0 (own and halo), input planes z0 and z0+1
+    Cells fa, fb;     // planes z + 2 and z + 3
+    ZStress sa, sb;   // own stress of planes z - 1 and z
+    Maps ma, mb;
+    {
+        cplx fm2[3];
+        Cells fm1, f0, f1;
+        real m0[NS], m1[NS], mh[NS];
+        load_cells(fm1, z0 - 1);
+        load_cells(f0, z0);
+        load_own(fm2, z0 - 2);
+        load_maps(m0, z0 - 1, xy0);
+        load_cells(f1, z0 + 1);
+        load_maps(m1, z0, xy0);
+        load_maps(mh, z0, xys);
+        load_cells(fa, z0 + 2);
+        load_step_maps(ma, z0);
+        put_plane(0, fm1);
+        put_plane(1, f0);
+        __syncthreads();
+        cplx s[6];
+        stress_at(sp + h0, fm2, f0.o, m0, s);
+        sa = ZStress{s[2], s[3], s[4]};
+        stress_at(sp + 3 * M::HP + h0, fm1.o, f1.o, m1, s);
+        sb = ZStress{s[2], s[3], s[4]};
+        put_own_stress(0, s);
+        if (st1) {
+            stress_at(sp + 3 * M::HP + h1, fm1.h, f1.h, mh, s);
+            put_stress(0, q1, s);
+        }
+        __syncthreads();
+        put_plane(0, f1);
+        __syncthreads();
     }
-    const real* rho = maps + (size_t)NS * cells;   // (uint32 offsets below)
-    real rho_z = rho[zoff(z0) + xy0], rho_1 = rho[zoff(z0 + 1) + xy0], rho_2 = rho[zoff(z0 + 2) + xy0];
-    __syncthreads();
 
     const real sc = pd.inv4dx2;
-    // step z: b on plane z; rd holds plane z+3 and is refilled with z+5
-    auto plane_step = [&](int z, Raw& rd0, Raw& rd1) {
-        // stress of plane z+1 at the own and inner-ring cells
-        cplx s0[6], s1[6];
-        if constexpr (GEN) {
-            load_maps(mc0, zoff(z + 1) + xy0);
-            if (st1) load_maps(mc1, zoff(z + 1) + xy1);
+    // step z (LDS copy K holds input plane z + 1 and stress plane z, the other
+    // input plane z): c = input plane z + 2; d receives plane z + 3; old = own
+    // stress of z - 1, replaced by that of z + 1
+    auto plane_step = [&](auto kc, int z, const Cells& c, Cells& d, ZStress& old, Maps& m, Maps& mn) {
+        constexpr int K = decltype(kc)::value;
+        real mm[NS];   // 21 constants: this step's maps, issued before the next plane
+        if constexpr (GEN) load_maps(mm, z + 1, xy0);
+        load_cells(d, z + 3);   // at the end of the range: planes that exist but are not used
+        load_step_maps(mn, z + 1);
+        cplx a[3], s0[6];
+        get_own(a, 1 - K);
+        const cplx* w = sp + K * 3 * M::HP;
+        if constexpr (GEN) stress_at(w + h0, a, c.o, mm, s0);
+        else stress_at(w + h0, a, c.o, m.o, s0);
+        const cplx* q = ss + (M::NB == 2 ? K : 0) * M::NL * M::SP + q0;
+        auto dxy = [&](int i, int off) { return csub(q[i * M::SP + off], q[i * M::SP - off]); };
+        const cplx bx = cadd(cadd(dxy(0, 1), dxy(4, M::SX)), csub(s0[4], old.xz));
+        const cplx by = cadd(cadd(dxy(4, 1), dxy(1, M::SX)), csub(s0[3], old.yz));
+        const cplx bz = cadd(cadd(dxy(3, 1), dxy(2, M::SX)), csub(s0[2], old.zz));
+        const cplx wr = cscale(pd.w2, m.rho);
+        cplx* o = bs + zoff(z);
+        if (FULL || own_xy) {   // a FULL column does not overhang the grid
+            st_wt(o + xy0, cadd(cmul(wr, a[0]), cscale(bx, sc)));
+            st_wt(o + cells + xy0, cadd(cmul(wr, a[1]), cscale(by, sc)));
+            st_wt(o + 2 * cells + xy0, cadd(cmul(wr, a[2]), cscale(bz, sc)));
         }
-        stress_at(h0, fa0, fc0, mc0, s0);
-        if (st1) stress_at(h1, fa1, fc1, mc1, s1);
-        // b on plane z at the own cell
-        if (own_xy) {
-            auto dxy = [&](int i, int off) { return csub(ss[i * M::SP + q0 + off], ss[i * M::SP + q0 - off]); };
-            const cplx bx = cadd(cadd(dxy(0, 1), dxy(5, M::SX)), csub(s0[4], sold[4]));
-            const cplx by = cadd(cadd(dxy(5, 1), dxy(1, M::SX)), csub(s0[3], sold[3]));
-            const cplx bz = cadd(cadd(dxy(4, 1), dxy(3, M::SX)), csub(s0[2], sold[2]));
-            const uint32_t g = zoff(z) + xy0;
-            const cplx wr = cscale(pd.w2, rho_z);
-            st_wt(bs + g, cadd(cmul(wr, fa0[0]), cscale(bx, sc)));
-            st_wt(bs + g + cells32, cadd(cmul(wr, fa0[1]), cscale(by, sc)));
-            st_wt(bs + g + 2 * cells32, cadd(cmul(wr, fa0[2]), cscale(bz, sc)));
-        }
-        __syncthreads();   // the LDS planes z+1 (input) and z (stress) are read
-#pragma unroll
-        for (int i = 0; i < 6; ++i) {   // own stress of plane z for the next z difference
-            sold[i] = ss[i * M::SP + q0];
-            ss[i * M::SP + q0] = s0[i];
-            if (st1) ss[i * M::SP + q1] = s1[i];
-        }
-        put_plane(fc0, fc1);
-#pragma unroll
-        for (int c = 0; c < 3; ++c) {
-            fa0[c] = fb0[c];
-            fb0[c] = fc0[c];
-            fa1[c] = fb1[c];
-            fb1[c] = fc1[c];
-        }
-        convert(rd0, fc0);
-        if (has1) convert(rd1, fc1);
-        if constexpr (!GEN) {
-#pragma unroll
-            for (int p = 0; p < NS; ++p) {
-                mc0[p] = mn0[p];
-                mc1[p] = mn1[p];
+        old = ZStress{s0[2], s0[3], s0[4]};
+        if constexpr (M::NB == 1) __syncthreads();   // the stress of plane z is read
+        put_own_stress(1 - K, s0);
+        if (st1) {
+            cplx s1[6];
+            get_halo(a, 1 - K);
+            if constexpr (GEN) {
+                load_maps(mm, z + 1, xy1);
+                stress_at(w + h1, a, c.h, mm, s1);
+            } else {
+                stress_at(w + h1, a, c.h, m.h, s1);
             }
+            put_stress(1 - K, q1, s1);
         }
-        rho_z = rho_1;
-        rho_1 = rho_2;
-        if (z + 5 <= z1 + 1) {
-            load_raw(rd0, zoff(z + 5) + xy0);
-            if (has1) load_raw(rd1, zoff(z + 5) + xy1);
-        }
-        if (z + 3 <= z1) {
-            if constexpr (!GEN) {
-                load_maps(mn0, zoff(z + 3) + xy0);
-                if (st1) load_maps(mn1, zoff(z + 3) + xy1);
-            }
-            rho_2 = rho[zoff(z + 3) + xy0];
-        }
+        put_plane(1 - K, c);
         __syncthreads();
     };
-    int z = z0;
-    for (; z + 1 < z1; z += 2) {
-        plane_step(z, rA0, rA1);
-        plane_step(z + 1, rB0, rB1);
+    using K0 = std::integral_constant<int, 0>;
+    using K1 = std::integral_constant<int, 1>;
+    for (int z = z0; z < z1; z += 2) {   // ranges hold an even number of planes
+        plane_step(K0{}, z, fa, fb, sa, ma, mb);
+        plane_step(K1{}, z + 1, fb, fa, sb, mb, ma);
     }
-    if (z < z1) plane_step(z, rA0, rA1);
 }
 
-template <bool GEN, int TX, int TY>
+template <bool GEN, int TX, int TY, bool FULL>
 static hipError_t stencil3z_launch(const StencilArgs& a, const ProbDev3& pd, const SysState* st, hipStream_t s) {
+    if (FULL && (pd.nx != TX || pd.ny % TY != 0)) return hipErrorInvalidValue;
     const int ntx = (pd.nx + TX - 1) / TX, nty = (pd.ny + TY - 1) / TY;
-    // z ranges of at most 32 planes, more of them while the launch is small
+    if (pd.nz % 4 != 0) return hipErrorInvalidValue;   // every supported length is a multiple of four
+    const size_t lds = march3_lds<TX, TY, FULL>();
+    // z ranges of ZC planes (a multiple of four, at most 32) by the plane steps
+    // one after the other: a range's steps, its start counted as four (three
+    // halo planes and their latency), times the rounds in which the chip takes
+    // the blocks (by LDS, and by the wavefronts per SIMD that the registers
+    // allow with a block's first wavefront on the first SIMD).  The shortest
+    // range within an eighth of the fewest steps, since the neighbours of a
+    // short range's halos are resident with it (80 x 40 x 32 x 100: 175 us by
+    // ranges of 16, 186 by 32); the fewest steps where a start loads 63 maps a
+    // cell (21 constants at 50 systems: 132 us by 32, 157 by 16).  Few blocks,
+    // against halving the range until there are 1024: 96 x 64 x 48 x 7
+    // 39.8 -> 36 us, 80 x 40 x 32 x 1 14.8 -> 9.7 us.
+    constexpr int kWaves = TX * TY / 64, kPerSimd = sizeof(real) == 8 ? 1 : GEN ? 3 : 4;
+    const int bpc = std::max(1, std::min((int)(kMaxLds / (lds + 64)), kPerSimd / ((kWaves + 3) / 4)));
+    auto steps = [&](int zc) -> long long {
+        const long long nb = (long long)ntx * nty * ((pd.nz + zc - 1) / zc) * pd.nsys;
+        return (nb + kCUs * bpc - 1) / (kCUs * bpc) * (zc + 4);
+    };
     int ZC = std::min(pd.nz, 32);
-    while (ZC > 8 && (long long)ntx * nty * ((pd.nz + ZC - 1) / ZC) * pd.nsys < 1024) ZC /= 2;
+    long long best = steps(ZC);
+    for (int zc = ZC - 4; zc >= 4; zc -= 4) best = std::min(best, steps(zc));
+    const long long limit = GEN ? best : best + best / 8;
+    if (GEN) {
+        while (steps(ZC) > limit) ZC -= 4;
+    } else {
+        for (ZC = 4; steps(ZC) > limit;) ZC += 4;
+    }
     const long long blocks = (long long)ntx * nty * ((pd.nz + ZC - 1) / ZC) * pd.nsys;
     if (blocks > 0x7fffffffLL) return hipErrorInvalidValue;
-    const size_t lds = march3_lds<TX, TY>();
-    hipError_t e = allow_lds(k_stencil3z<GEN, TX, TY>, lds);
+    hipError_t e = allow_lds(k_stencil3z<GEN, TX, TY, FULL>, lds);
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL((k_stencil3z<GEN, TX, TY>), dim3((unsigned)blocks), dim3(TX * TY), lds, s, a.u, a.b, a.maps,
+    hipLaunchKernelGGL((k_stencil3z<GEN, TX, TY, FULL>), dim3((unsigned)blocks), dim3(TX * TY), lds, s, a.u, a.b, a.maps,
                        pd, ZC, st);
     return hipGetLastError();
 }
@@ -585,22 +638,29 @@ static hipError_t stencil3_launch(const StencilArgs& a, const ProbDev3& pd, SysS
     return hipGetLastError();
 }
 
-// Column shape of the z-marching stencil (256 threads): 16 x 16 or 32 x 8
-// cells, whichever overhangs the grid less; 0 for grids thinner than 8 cells
-// in y, which take the tiled kernel.  (A 16 x 20 column, which loads a fifth
-// fewer cells per plane at 80 x 40, was slower: five waves per block pack
-// worse than four.)
-static int march_shape(int nx, int ny) {
-    if (ny < 8 || nx < 16) return 0;
-    const long long a = (long long)((nx + 15) / 16) * 16 * ((ny + 15) / 16) * 16;
-    const long long b = (long long)((nx + 31) / 32) * 32 * ((ny + 7) / 8) * 8;
-    return a <= b ? 16 : 32;
+// Whether a grid takes the z-marching stencil: not one thinner than 8 cells
+// in y, which takes the tiled kernel.
+static bool march_ok(const ProbDev3& pd) { return pd.ny >= 8 && pd.nx >= 16; }
+
+template <bool GEN>
+static hipError_t stencil3z_any(const StencilArgs& a, const ProbDev3& pd, const SysState* st, hipStream_t s) {
+#ifndef FW_C128
+#define FW_FULL(X, Y) \
+    if (pd.nx == X && pd.ny % Y == 0) return stencil3z_launch<GEN, X, Y, true>(a, pd, st, s);
+    FW_FULL(16, 16) FW_FULL(24, 8) FW_FULL(32, 8) FW_FULL(40, 8) FW_FULL(48, 4) FW_FULL(64, 4) FW_FULL(80, 4)
+    FW_FULL(96, 4) FW_FULL(128, 4)
+#undef FW_FULL
+#endif
+    // 16 x 16 or 32 x 8 cells, whichever overhangs the grid less
+    const long long q = (long long)((pd.nx + 15) / 16) * 16 * ((pd.ny + 15) / 16) * 16;
+    const long long r = (long long)((pd.nx + 31) / 32) * 32 * ((pd.ny + 7) / 8) * 8;
+    return q <= r ? stencil3z_launch<GEN, 16, 16, false>(a, pd, st, s)
+                  : stencil3z_launch<GEN, 32, 8, false>(a, pd, st, s);
 }
 
 template <int VM, bool GEN>
 static hipError_t stencil3_any(const StencilArgs& a, const ProbDev3& pd, SysState* st, hipStream_t s) {
-    const int m = march_shape(pd.nx, pd.ny);
-    if (m == 0) return stencil3_launch<VM, GEN>(a, pd, st, s);   // the tiled kernel, update fused
+    if (!march_ok(pd)) return stencil3_launch<VM, GEN>(a, pd, st, s);   // the tiled kernel, update fused
     StencilArgs p = a;
     if constexpr (VM != VM_NONE) {
         // the vector update as its own streaming pass, then the plain
@@ -611,7 +671,7 @@ static hipError_t stencil3_any(const StencilArgs& a, const ProbDev3& pd, SysStat
         if (e != hipSuccess) return e;
         p.u = a.wout;
     }
-    return m == 16 ? stencil3z_launch<GEN, 16, 16>(p, pd, st, s) : stencil3z_launch<GEN, 32, 8>(p, pd, st, s);
+    return stencil3z_any<GEN>(p, pd, st, s);
 }
 
 template <bool GEN>

@@ -33,6 +33,7 @@ enum ColMode : int { COL_GREEN = 0, COL_FWD = 1, COL_INV = 2 };
 bool fft_size_supported(int n);
 
 constexpr size_t kMaxLds = 160 * 1024;   // LDS per workgroup on gfx950
+constexpr int kCUs = 256;                // compute units of an MI355X
 
 // Kernel variants of one problem (chosen by the autotuner or the caller).
 struct ColCfg {

@@ -97,6 +97,21 @@ def test_marching_stencil_column_shapes(nx, ny, nz):
     assert _rel(_np(plan.view(plan.body_force(ut), 0)), P.body_force(u)) < KERNEL_TOL
 
 
+@pytest.mark.parametrize("params", ["vti", "general"])
+@pytest.mark.parametrize("nx,ny,nz,nsys", [
+    (16, 16, 20, 2), (24, 24, 16, 1), (40, 16, 16, 1), (48, 20, 16, 3), (64, 16, 40, 1), (80, 20, 16, 1),
+    (96, 16, 20, 1), (128, 16, 16, 1),   # columns as wide as the grid, ranges that do not divide nz
+    (20, 40, 16, 2), (40, 20, 16, 1), (160, 16, 16, 1),   # narrower columns, with and without overhang
+])
+def test_marching_stencil_wide_columns(nx, ny, nz, nsys, params):
+    """Column shapes of the z-marching stencil that wrap in x, and their z
+    ranges, against the oracle's contrast stencil."""
+    print(f"3-D stencil {nx}x{ny}x{nz} x {nsys} {params}", flush=True)
+    plan, p, maps, P = _case(nx, ny, nz, nsys, params)
+    u = _field(np.random.default_rng(8), nsys, nx, ny, nz)
+    assert _rel(_np(plan.view(plan.body_force(plan.pack([u])), 0)), P.body_force(u)) < KERNEL_TOL
+
+
 @pytest.mark.parametrize("nx,ny,nz,nsys", [
     (16, 16, 20, 3),     # several planes per block, the smallest radices
     (20, 24, 16, 1), (24, 20, 32, 2), (32, 160, 16, 1), (48, 32, 24, 2), (256, 16, 16, 1), (16, 256, 16, 1),
