@@ -326,7 +326,8 @@ __device__ __forceinline__ void twiddles(cplx (&w)[R], const cplx* __restrict__ 
     w[1] = w1;
     if constexpr (R >= 3) w[2] = cmul(w1, w1);
     if constexpr (R >= 4) w[3] = cmul(w[2], w1);
-    if constexpr (R == 5) w[4] = cmul(w[3], w1);
+    if constexpr (R == 5 || R == 6) w[4] = cmul(w[2], w[2]);
+    if constexpr (R == 6) w[5] = cmul(w[3], w[2]);
     if constexpr (R >= 8) {
         cplx w4 = tw[4 * e];
         if (INV) w4 = cconj(w4);
@@ -353,6 +354,15 @@ __device__ __forceinline__ void twiddles(cplx (&w)[R], const cplx* __restrict__ 
 #pragma unroll
         for (int r = 17; r < R; ++r) w[r] = cmul(w16, w[r - 16]);
     }
+}
+
+// x[k] *= W_N^(k e) (conjugated for the inverse), k = 1..R-1.
+template <int R, bool INV>
+__device__ __forceinline__ void twiddle_all(cplx (&x)[R], const cplx* __restrict__ tw, int e) {
+    cplx w[R];
+    twiddles<R, INV>(w, tw, e);
+#pragma unroll
+    for (int k = 1; k < R; ++k) x[k] = cmul(x[k], w[k]);
 }
 
 // The R outputs of a butterfly with autosort base `base`: x[r] to position

@@ -4,14 +4,14 @@
 //   k_stencil3        - contrast stencil b = w~^2 drho u + div_h(dC : E_h u) on
 //                       [nsys][3][nz][ny][nx] fields, with the BiCGSTAB vector
 //                       update of its input fused into the load (bicg.h);
-//   k_axis            - FFT along y or z (a strided axis) in place, and the z
-//                       pass that multiplies by the 3 x 3 Green's tensor
-//                       G_hat(k) = (Gamma(k) - rho0 w~^2 I)^-1 between its
-//                       forward and inverse transforms;
+//   k_axis            - FFT along y or z (a strided axis) in place;
+//   k_green3          - the z transforms around the multiplication by the 3 x 3
+//                       Green's tensor G_hat(k) = (Gamma(k) - rho0 w~^2 I)^-1;
 //   k_point_sources3, k_gather3, k_scatter_conj3 - sources and receivers;
 //   k_correlate3      - the adjoint correlation of eq. ad1 summed over
 //                       systems in FP64.
-// The x transforms are the row kernels of the 2-D path (rows of nx points).
+// The x transforms are the row kernels of the 2-D path (rows of nx points), or
+// with the y transforms the plane kernels (plane_kernels.h).
 #include <algorithm>
 #include <numeric>
 #include <type_traits>
@@ -691,10 +691,9 @@ hipError_t launch_stencil3(int vm, const StencilArgs& a, const ProbDev3& pd, Sys
 
 // ------------------------------------------------------ strided axes -----
 // Transforms along an axis of length N with stride S (the product of the
-// faster dimensions): the data is [nslab][N][S] (AX_FWD, AX_INV: one slab per
-// (system, component, outer index)) or [nsys][3][N][S] (AX_GREEN: the z pass
-// of the three components of one system).  A block takes W adjacent columns
-// of one slab; thread (t, c) holds positions t + T m of column c.
+// faster dimensions): the data is [nslab][N][S], one slab per (system,
+// component, outer index).  A block takes W adjacent columns of one slab;
+// thread (t, c) holds positions t + T m of column c.
 struct AxisLds {
     cplx* base;
     int stride, PL;
@@ -730,14 +729,12 @@ __device__ __forceinline__ real axis_k(int i, int n, real dk, real dx, bool cent
     return central ? rsinpi(2.0f * (real)si / (real)n) / dx : (real)si * dk;
 }
 
-template <int N, int P, int MODE>
+template <int N, int P, bool INV>
 __global__ __launch_bounds__(256) void k_axis(cplx* __restrict__ data, int S, int W, int slabs_per_sys,
-                                              const SysState* __restrict__ st, const cplx* __restrict__ tw,
-                                              ProbDev3 pd, PlaneOrder ord) {
+                                              const SysState* __restrict__ st, const cplx* __restrict__ tw) {
     using FS = FftShape<N, P>;
     constexpr int T = FS::T;
     constexpr int PL = PaddedLen<N>::value;
-    constexpr int NC = MODE == AX_GREEN ? 3 : 1;
     extern __shared__ cplx lds_dyn[];
 
     const int tid = threadIdx.x;
@@ -746,21 +743,80 @@ __global__ __launch_bounds__(256) void k_axis(cplx* __restrict__ data, int S, in
     const int blk = xcd_remap(blockIdx.x, gridDim.x);
     const int slab = blk / ncb;
     const int col = (blk - slab * ncb) * W + c;
-    const int sys = MODE == AX_GREEN ? slab : slab / slabs_per_sys;
-    if (st != nullptr && st[sys].status != ST_RUNNING) return;
+    if (st != nullptr && st[slab / slabs_per_sys].status != ST_RUNNING) return;
     const bool active = t < T;
-    const size_t span = (size_t)N * S;
-    cplx* base = data + (size_t)slab * NC * span + col;
+    cplx* base = data + (size_t)slab * N * S + col;
 
-    cplx v[NC][P];
+    cplx v[1][P];
 #pragma unroll
-    for (int f = 0; f < NC; ++f)
+    for (int m = 0; m < P; ++m) v[0][m] = active ? base[(size_t)(t + T * m) * S] : mkc(0.f, 0.f);
+    AxisLds lds{active ? lds_dyn + c : lds_dyn + (size_t)PL * W, active ? W : 1, PL};
+    fft_run<N, P, INV, 1>(v, active ? t : 0, tw, lds);
+    if (active) {
 #pragma unroll
-        for (int m = 0; m < P; ++m) v[f][m] = active ? base[f * span + (size_t)(t + T * m) * S] : mkc(0.f, 0.f);
-    AxisLds lds{active ? lds_dyn + c : lds_dyn + (size_t)NC * PL * W, active ? W : 1, PL};
-    const int tt = active ? t : 0;
-    if constexpr (MODE != AX_INV) fft_run<N, P, false, NC>(v, tt, tw, lds);
-    if constexpr (MODE == AX_GREEN) {
+        for (int m = 0; m < P; ++m) st_wt(base + (size_t)(t + T * m) * S, v[0][m]);
+    }
+}
+
+// ------------------------------------------------------------- z pass -----
+// z transforms of the three components of W columns, the 3 x 3 Green multiply
+// and the inverse transforms, in place on [nsys][3][N][S].  As in the plane
+// passes, N = R1 R2 and a transform is two sweeps in place in LDS:
+//   1. a butterfly of radix R1 of one component per item, from memory;
+//   2. the radix-R2 butterflies of all three components per item, the Green
+//      multiply of the R2 wavenumbers k1 + R1 k2 it then holds, and the
+//      inverse butterflies;
+//   3. sweep 1 undone, to memory.
+// Small radices in sweep 2 keep the three components of an item in few
+// registers.  Along a column the six entries of Gamma' are quadratic in kz,
+// with coefficients formed once per column (36 -> 12 multiply-adds per
+// wavenumber).  Against all points of three components in one thread
+// (two wavefronts per SIMD at 12 points): 32 points at 80 x 40 x 100 90 -> 83
+// us (a read and a write of the field at the rate of a large copy take 96,
+// part of it stays in the memory-side cache), 48 points at 96 x 64 x 7 35.5 ->
+// 20.1 us, 64 points at 64 x 64 x 32 79 -> 61 us.
+template <int N>
+struct GreenShape {
+    static constexpr int R2 = N < 128 ? 4 : 8, R1 = N / R2;
+};
+
+constexpr int kGreenThreads = sizeof(real) == 8 ? 256 : 512;   // complex128 needs the registers
+
+template <int N, int W>
+__global__ __launch_bounds__(kGreenThreads) void k_green3(cplx* __restrict__ data, int S, const SysState* __restrict__ st,
+                                                const cplx* __restrict__ tw, ProbDev3 pd, PlaneOrder ord) {
+    constexpr int R1 = GreenShape<N>::R1, R2 = GreenShape<N>::R2;
+    extern __shared__ cplx lds_dyn[];   // [3][N][W]
+    const int ncb = S / W, nt = blockDim.x;
+    const int blk = xcd_remap(blockIdx.x, gridDim.x);
+    const int sys = blk / ncb;
+    if (st != nullptr && st[sys].status != ST_RUNNING) return;
+    const int col0 = (blk - sys * ncb) * W;
+    cplx* base = data + (size_t)sys * 3 * N * S + col0;
+
+    for (int i = threadIdx.x; i < 3 * R2 * W; i += nt) {
+        const int c = i % W, q = i / W, f = q / R2, n2 = q - f * R2;
+        const cplx* s = base + ((size_t)f * N + n2) * S + c;
+        cplx v[R1];
+#pragma unroll
+        for (int k = 0; k < R1; ++k) v[k] = s[(size_t)k * R2 * S];
+        dft<R1, false>(v);
+        twiddle_all<R1, false>(v, tw, n2);
+        cplx* p = lds_dyn + (f * N + n2) * W + c;
+#pragma unroll
+        for (int k = 0; k < R1; ++k) p[k * R2 * W] = v[k];
+    }
+    __syncthreads();
+    for (int i = threadIdx.x; i < R1 * W; i += nt) {
+        const int c = i % W, k1 = i / W, col = col0 + c;
+        cplx* p = lds_dyn + k1 * R2 * W + c;
+        cplx v[3][R2];
+#pragma unroll
+        for (int f = 0; f < 3; ++f) {
+#pragma unroll
+            for (int k = 0; k < R2; ++k) v[f][k] = p[(f * N + k) * W];
+            dft<R2, false>(v[f]);
+        }
         int ix = col % pd.nx, iy = col / pd.nx;
         if (ord.planes) {   // column y + ny x of the positions R2 k1 + k2
             const int px = col / pd.ny, py = col - px * pd.ny;
@@ -773,35 +829,47 @@ __global__ __launch_bounds__(256) void k_axis(cplx* __restrict__ data, int S, in
         // products of two different components: 0 at an even axis's Nyquist index
         const real kxo = (pd.nx % 2 == 0 && ix == pd.nx / 2) ? 0.f : kx;
         const real kyo = (pd.ny % 2 == 0 && iy == pd.ny / 2) ? 0.f : ky;
+        real g0[6], g1[6];   // Gamma'_p = g0 + g1 kzo + gq kz^2
 #pragma unroll
-        for (int m = 0; m < P; ++m) {
-            const int iz = tt + T * m;
+        for (int e = 0; e < 6; ++e) {
+            g0[e] = pd.gq[e][0] * (kx * kx) + pd.gq[e][1] * (ky * ky) + pd.gq[e][5] * (kxo * kyo);
+            g1[e] = pd.gq[e][3] * kyo + pd.gq[e][4] * kxo;
+        }
+#pragma unroll
+        for (int k = 0; k < R2; ++k) {
+            const int iz = k1 + R1 * k;
             const real kz = axis_k(iz, N, pd.dk[2], pd.dx, central);
             const real kzo = (N % 2 == 0 && iz == N / 2) ? 0.f : kz;
-            const real mono[6] = {kx * kx, ky * ky, kz * kz, kyo * kzo, kxo * kzo, kxo * kyo};
+            const real kz2 = kz * kz;
             real g[6];
 #pragma unroll
-            for (int p = 0; p < 6; ++p) {
-                real a = 0;
-#pragma unroll
-                for (int q = 0; q < 6; ++q) a += pd.gq[p][q] * mono[q];
-                g[p] = a;
-            }
-            cplx b3[3] = {v[0][m], v[1][m], v[2][m]};
+            for (int e = 0; e < 6; ++e) g[e] = g0[e] + (g1[e] * kzo + pd.gq[e][2] * kz2);
+            cplx b3[3] = {v[0][k], v[1][k], v[2][k]};
             green_mul3(b3, g, pd.ga, pd.gscale);
-            v[0][m] = b3[0];
-            v[1][m] = b3[1];
-            v[2][m] = b3[2];
+            v[0][k] = b3[0];
+            v[1][k] = b3[1];
+            v[2][k] = b3[2];
             __builtin_amdgcn_sched_barrier(0);   // one point at a time: bounded registers
         }
-        __syncthreads();
+#pragma unroll
+        for (int f = 0; f < 3; ++f) {
+            dft<R2, true>(v[f]);
+#pragma unroll
+            for (int k = 0; k < R2; ++k) p[(f * N + k) * W] = v[f][k];
+        }
     }
-    if constexpr (MODE != AX_FWD) fft_run<N, P, true, NC>(v, tt, tw, lds);
-    if (active) {
+    __syncthreads();
+    for (int i = threadIdx.x; i < 3 * R2 * W; i += nt) {
+        const int c = i % W, q = i / W, f = q / R2, n2 = q - f * R2;
+        const cplx* p = lds_dyn + (f * N + n2) * W + c;
+        cplx v[R1];
 #pragma unroll
-        for (int f = 0; f < NC; ++f)
+        for (int k = 0; k < R1; ++k) v[k] = p[k * R2 * W];
+        twiddle_all<R1, true>(v, tw, n2);
+        dft<R1, true>(v);
+        cplx* o = base + ((size_t)f * N + n2) * S + c;
 #pragma unroll
-            for (int m = 0; m < P; ++m) st_wt(base + f * span + (size_t)(t + T * m) * S, v[f][m]);
+        for (int k = 0; k < R1; ++k) st_wt(o + (size_t)k * R2 * S, v[k]);
     }
 }
 
@@ -819,23 +887,51 @@ bool axis3_size_supported(int n) {
     return false;
 }
 
-template <int N, int MODE>
+template <int N, bool INV>
 static hipError_t axis_launch(cplx* data, int S, int nslab, int slabs_per_sys, const SysState* st, const cplx* tw,
-                              const ProbDev3& pd, hipStream_t s, const PlaneOrder& ord = PlaneOrder{}) {
+                              hipStream_t s) {
     constexpr int P = (N % 5 == 0) ? 10 : (N % 3 == 0) ? 12 : 8;
     constexpr int T = N / P;
-    constexpr int NC = MODE == AX_GREEN ? 3 : 1;
     int W = 16;
     while (W > 1 && (W * T > 256 || S % W != 0)) W /= 2;
     const int threads = ((W * T + 63) / 64) * 64;
-    const size_t lds = (size_t)(NC * PaddedLen<N>::value * (W + 1)) * sizeof(cplx);
-    hipError_t e = allow_lds(k_axis<N, P, MODE>, lds);
+    const size_t lds = (size_t)(PaddedLen<N>::value * (W + 1)) * sizeof(cplx);
+    hipError_t e = allow_lds(k_axis<N, P, INV>, lds);
     if (e != hipSuccess) return e;
     const long long blocks = (long long)nslab * (S / W);
     if (blocks > 0x7fffffffLL) return hipErrorInvalidValue;
-    hipLaunchKernelGGL((k_axis<N, P, MODE>), dim3((unsigned)blocks), dim3(threads), lds, s, data, S, W,
-                       slabs_per_sys, st, tw + twiddle_offset(N), pd, ord);
+    hipLaunchKernelGGL((k_axis<N, P, INV>), dim3((unsigned)blocks), dim3(threads), lds, s, data, S, W, slabs_per_sys,
+                       st, tw + twiddle_offset(N));
     return hipGetLastError();
+}
+
+template <int N, int W>
+static hipError_t green3_launch(cplx* data, int S, int nsys, const SysState* st, const cplx* tw, const ProbDev3& pd,
+                                const PlaneOrder& ord, hipStream_t s) {
+    using G = GreenShape<N>;
+    const size_t lds = (size_t)3 * N * W * sizeof(cplx);
+    hipError_t e = allow_lds(k_green3<N, W>, lds);
+    if (e != hipSuccess) return e;
+    const long long blocks = (long long)nsys * (S / W);
+    if (blocks > 0x7fffffffLL) return hipErrorInvalidValue;
+    const int items = std::max(3 * G::R2 * W, G::R1 * W);
+    const int threads = std::min(kGreenThreads, (items + 63) / 64 * 64);
+    hipLaunchKernelGGL((k_green3<N, W>), dim3((unsigned)blocks), dim3(threads), lds, s, data, S, st,
+                       tw + twiddle_offset(N), pd, ord);
+    return hipGetLastError();
+}
+
+// 16 columns per block (a full cache line of each plane), 8 where those would
+// leave LDS for two blocks per CU only or do not divide the plane, 4 for the
+// lengths that are odd multiples of 4 on grids one cell thick.
+template <int N>
+static hipError_t green3_any(cplx* data, int S, int nsys, const SysState* st, const cplx* tw, const ProbDev3& pd,
+                             const PlaneOrder& ord, hipStream_t s) {
+    if constexpr ((size_t)3 * N * 16 * sizeof(cplx) <= kMaxLds / 3)
+        if (S % 16 == 0) return green3_launch<N, 16>(data, S, nsys, st, tw, pd, ord, s);
+    if (S % 8 == 0) return green3_launch<N, 8>(data, S, nsys, st, tw, pd, ord, s);
+    if (S % 4 == 0) return green3_launch<N, 4>(data, S, nsys, st, tw, pd, ord, s);
+    return hipErrorInvalidValue;
 }
 
 hipError_t launch_axis3(int mode, int n, cplx* data, int S, int nslab, int slabs_per_sys, const SysState* st,
@@ -846,11 +942,11 @@ hipError_t launch_axis3(int mode, int n, cplx* data, int S, int nslab, int slabs
         ord = PlaneOrder{1, plane_radix(pd.nx), pd.nx / plane_radix(pd.nx), plane_radix(pd.ny),
                          pd.ny / plane_radix(pd.ny)};
     }
-#define FW_AX(N)                                                                                             \
-    if (n == N) {                                                                                            \
-        if (mode == AX_FWD) return axis_launch<N, AX_FWD>(data, S, nslab, slabs_per_sys, st, tw, pd, s);     \
-        if (mode == AX_INV) return axis_launch<N, AX_INV>(data, S, nslab, slabs_per_sys, st, tw, pd, s);     \
-        if (mode == AX_GREEN) return axis_launch<N, AX_GREEN>(data, S, nslab, slabs_per_sys, st, tw, pd, s, ord); \
+#define FW_AX(N)                                                                                     \
+    if (n == N) {                                                                                    \
+        if (mode == AX_FWD) return axis_launch<N, false>(data, S, nslab, slabs_per_sys, st, tw, s);  \
+        if (mode == AX_INV) return axis_launch<N, true>(data, S, nslab, slabs_per_sys, st, tw, s);   \
+        if (mode == AX_GREEN) return green3_any<N>(data, S, nslab, st, tw, pd, ord, s);              \
     }
     FW_AXIS_SIZES(FW_AX)
 #undef FW_AX

@@ -31,15 +31,6 @@ struct PlaneShape {
     static constexpr int NP = NX * NY;
 };
 
-// x[k] *= W_N^(k e) (conjugated for the inverse), k = 1..R-1.
-template <int R, bool INV>
-__device__ __forceinline__ void twiddle_all(cplx (&x)[R], const cplx* __restrict__ tw, int e) {
-    cplx w[R];
-    twiddles<R, INV>(w, tw, e);
-#pragma unroll
-    for (int k = 1; k < R; ++k) x[k] = cmul(x[k], w[k]);
-}
-
 // One butterfly of radix R in place on R LDS elements STRIDE apart.
 template <int R, bool INV, int STRIDE>
 __device__ __forceinline__ void sweep_lds(cplx* p) {

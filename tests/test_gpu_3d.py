@@ -136,6 +136,23 @@ def test_plane_transforms(nx, ny, nz, nsys):
     assert _rel(P.apply(x), u) < 2e-5 + KERNEL_TOL
 
 
+@pytest.mark.parametrize("precision", ["c64", "c128"])
+@pytest.mark.parametrize("nx,ny,nz", [
+    (16, 16, 16), (16, 16, 20), (16, 16, 24), (16, 16, 48), (16, 16, 80), (16, 16, 96), (16, 16, 128),   # 16 columns
+    (16, 16, 160), (16, 16, 192), (16, 16, 256), (24, 1, 40), (40, 1, 64),                               # 8 columns
+    (20, 1, 32),                                                                                         # 4 columns
+])
+def test_z_pass_lengths(nx, ny, nz, precision):
+    """The z pass at every radix pair and block width: convolution with the
+    general medium's Green's tensor against the oracle (rounding errors of
+    1e-7 and 1e-16 times the Green's tensor's own amplification)."""
+    print(f"z pass {nx}x{ny}x{nz} {precision}", flush=True)
+    plan, p, maps, P = _case(nx, ny, nz, 2, "general", precision=precision)
+    u = _field(np.random.default_rng(9), 2, nx, ny, nz)
+    tol = KERNEL_TOL if precision == "c64" else 1e-12
+    assert _rel(_np(plan.view(plan.convolve(plan.pack([u])), 0)), P.convolve(u)) < tol
+
+
 @pytest.mark.parametrize("params", ["vti", "general"])
 def test_solve_3d_matches_oracle_batched_plain_gmres(params):
     nx, ny, nz = 24, 20, 16
