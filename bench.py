@@ -87,7 +87,8 @@ PASS_MATCH = [lambda n: ((n.startswith("void fw::c64::k_body_force<") or n.start
               or re.search(r"c64::\(anonymous namespace\)::k_srows<\d+, \d+, 0, \d+>\(", n) is not None,
               lambda n: n.startswith("void fw::c64::k_rows<") and ", false, 0>" in n,
               lambda n: (n.startswith("void fw::c64::k_cols<") and ", 0, " in n)
-              or n.startswith("void fw::c64::k_cols_split<") or n.startswith("void fw::c64::k_cols_tw<"),
+              or n.startswith(("void fw::c64::k_cols_split<", "void fw::c64::k_cols_tw<",
+                               "void fw::c64::k_cols_sweep<")),
               lambda n: n.startswith("void fw::c64::k_rows<") and ", true, 1>" in n,
               lambda n: re.search(r"c64::\(anonymous namespace\)::k_srows<\d+, \d+, 3, \d+>\(", n) is not None]
 
@@ -271,6 +272,15 @@ def _pass_instance(k, tuning, n=256):
             return f"fw::c64::k_cols_split<{n}, {tuning['col_points']}>"
         if tuning["col_shared"] == 4:   # twiddles in LDS, compile-time tile width
             return f"fw::c64::k_cols_tw<{n}, {tuning['col_points']}, {tuning['col_width']}>"
+        if tuning["col_shared"] == 1 and tuning["col_width"] in (4, 8, 16):
+            p, w = tuning["col_points"], tuning["col_width"]
+            if p == (12 if n % 3 == 0 else 8):   # the default variant: radix sweeps, or twiddles in LDS
+                if n <= (384 if n % 3 == 0 else 128):
+                    while w > 4 and 3 * 16 * n * w > 160 * 1024:
+                        w //= 2
+                    return f"fw::c64::k_cols_sweep<{n}, {w}>"
+                if n in (256, 512):
+                    return f"fw::c64::k_cols_tw<{n}, 8, {min(w, 8)}>"
         seq = "true" if tuning["col_shared"] else "false"
         nt = 1024 if tuning["col_shared"] == 3 else 512
         return f"fw::c64::k_cols<{n}, {tuning['col_points']}, 0, {seq}, {nt}>"

@@ -472,7 +472,10 @@ typedef struct {
     int32_t row_points;    /* row-transform points per thread (radix sequence) */
     int32_t col_points;    /* column-transform points per thread */
     int32_t col_width;     /* columns per column workgroup (power of two) */
-    int32_t col_shared;    /* 1: the two components share one LDS buffer;
+    int32_t col_shared;    /* 1: the two components share one LDS buffer
+                                 (with the default col_points of a length and
+                                 tiles of 4 to 16 columns: the library's own
+                                 choice of pass for that length);
                               2: separate threads transform them;
                               3: as 1 in blocks of up to 1024 threads
                                  (complex64, power-of-two columns of 512 or

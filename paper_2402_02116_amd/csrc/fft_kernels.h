@@ -8,6 +8,8 @@
 // instantiates it from here.
 #pragma once
 
+#include <algorithm>
+
 #include "fft.h"
 #include "launch.h"
 
@@ -254,14 +256,13 @@ __device__ __forceinline__ void green_mul(cplx& bx, cplx& bz, real gxx, real gzz
 // Signed FFT index of i on an n-point axis (numpy fftfreq order).
 __device__ __forceinline__ int fft_signed(int i, int n) { return (i < (n + 1) / 2) ? i : i - n; }
 
-// u_hat = G_hat(k) b_hat(k) at the P points t + T*m of column ix of a
+// u_hat = G_hat(k) b_hat(k) at the P points t + T*m (T = N / P) of column ix of a
 // transformed spectrum, with the IFFT normalisation folded in (eqs. u0 and A
 // in the wavenumber domain).  The central-difference symbol sin(2 pi iz / N)
 // / dx comes from the twiddle table (tw[iz] = exp(-2 pi i iz / N)).
 template <int N, int P>
-__device__ __forceinline__ void green_column(cplx (&v)[2][P], int t, int ix, const ProbDev& pd,
+__device__ __forceinline__ void green_column(cplx (&v)[2][P], int t, int T, int ix, const ProbDev& pd,
                                              const cplx* tw) {
-    constexpr int T = N / P;
     const int nx = pd.nx;
     const int sx = fft_signed(ix, nx);
     const bool central = pd.symbol == 1;
@@ -330,7 +331,7 @@ __global__ __launch_bounds__(NT) void k_cols(cplx* __restrict__ data, ProbDev pd
         else fft_run<N, P, false, 2>(v, tt, tw, lds);
     }
     if constexpr (MODE == COL_GREEN) {
-        green_column<N, P>(v, tt, x0 + c, pd, tw);
+        green_column<N, P>(v, tt, T, x0 + c, pd, tw);
         __syncthreads();
     }
     if constexpr (MODE != COL_FWD) {
@@ -479,7 +480,7 @@ __global__ __launch_bounds__(512) void k_cols_tw(cplx* __restrict__ data, ProbDe
     __syncthreads();   // the twiddle table is in LDS
 
     fft_run<N, P, false, 2, true>(v, t, lds_dyn, lds);
-    green_column<N, P>(v, t, ix, pd, lds_dyn);
+    green_column<N, P>(v, t, T, ix, pd, lds_dyn);
     // as in k_cols: opaque copies keep the forward pass's twiddles and LDS
     // addresses from being held in registers across the Green multiply
     int toff = 0;
@@ -492,6 +493,89 @@ __global__ __launch_bounds__(512) void k_cols_tw(cplx* __restrict__ data, ProbDe
     for (int f = 0; f < 2; ++f)
 #pragma unroll
         for (int m = 0; m < P; ++m) st_wt(base + f * plane + (size_t)(t + T * m) * cs, v[f][m]);
+}
+
+// The Green-multiply column pass as two radix sweeps in place in LDS (N = R1
+// R2, as in the 3-D passes): a butterfly of radix R1 of one component per item,
+// from memory; then the radix-R2 butterflies of both components, the Green
+// multiply of the R2 wavenumbers k1 + R1 k2 that the item then holds, and the
+// inverse butterflies; then sweep 1 undone, to memory.  Two LDS round trips and
+// two barriers where the autosort passes of both directions take four to twelve
+// barriers, and no value of one direction is held across the other.
+template <int N>
+struct ColSweep {
+    static constexpr int R1 = N == 16 ? 4 : N == 24 ? 6 : N == 32 || N == 64 ? 8 : N == 48 || N == 96 ? 12
+                              : N == 128 || (N == 192 && sizeof(real) == 4) ? 16 : 24;
+    static constexpr int R2 = N / R1;
+};
+// Lengths with a sweep pass: 2^k up to 128 and 3 2^k up to 384 points.  Longer
+// ones need radices whose butterflies of two components leave three wavefronts
+// per SIMD or fewer: 256 points by 32 x 8 27 us at 256^2 x 64, 22 us by the
+// autosort passes with their twiddles in LDS; complex128 spills beyond 192.
+constexpr bool col_sweep_size(int n) {
+    return n % 3 == 0 ? n <= (sizeof(real) == 8 ? 192 : 384) : n <= 128;
+}
+
+template <int N, int W>
+__global__ __launch_bounds__(512) void k_cols_sweep(cplx* __restrict__ data, ProbDev pd,
+                                                     const SysState* __restrict__ st,
+                                                     const cplx* __restrict__ tw) {
+    constexpr int R1 = ColSweep<N>::R1, R2 = ColSweep<N>::R2;
+    extern __shared__ cplx lds_dyn[];   // [2][N][W]
+    const int nx = pd.nx, nt = blockDim.x;
+    const int ntile = nx / W;
+    const int blk = xcd_remap(blockIdx.x, gridDim.x);
+    const int sys = blk / ntile;
+    if (st != nullptr && st[sys].status != ST_RUNNING) return;
+    const int x0 = (blk - sys * ntile) * W;
+    const size_t plane = (size_t)N * nx;
+    const int cs = pd.tile_sh ? (1 << pd.tile_sh) : nx;   // column stride: row-major or column-tiled
+    cplx* base = data + (size_t)sys * 2 * plane + spec_off(0, x0, nx, pd.tile_sh ? N : 0, pd.tile_sh);
+
+    for (int i = threadIdx.x; i < 2 * R2 * W; i += nt) {
+        const int c = i % W, q = i / W, f = q / R2, n2 = q - f * R2;
+        const cplx* s = base + f * plane + (size_t)n2 * cs + c;
+        cplx v[R1];
+#pragma unroll
+        for (int k = 0; k < R1; ++k) v[k] = s[(size_t)k * R2 * cs];
+        dft<R1, false>(v);
+        twiddle_all<R1, false>(v, tw, n2);
+        cplx* p = lds_dyn + (f * N + n2) * W + c;
+#pragma unroll
+        for (int k = 0; k < R1; ++k) p[k * R2 * W] = v[k];
+    }
+    __syncthreads();
+    for (int i = threadIdx.x; i < R1 * W; i += nt) {
+        const int c = i % W, k1 = i / W;
+        cplx* p = lds_dyn + k1 * R2 * W + c;
+        cplx v[2][R2];
+#pragma unroll
+        for (int f = 0; f < 2; ++f) {
+#pragma unroll
+            for (int k = 0; k < R2; ++k) v[f][k] = p[(f * N + k) * W];
+            dft<R2, false>(v[f]);
+        }
+        green_column<N, R2>(v, k1, R1, x0 + c, pd, tw);
+#pragma unroll
+        for (int f = 0; f < 2; ++f) {
+            dft<R2, true>(v[f]);
+#pragma unroll
+            for (int k = 0; k < R2; ++k) p[(f * N + k) * W] = v[f][k];
+        }
+    }
+    __syncthreads();
+    for (int i = threadIdx.x; i < 2 * R2 * W; i += nt) {
+        const int c = i % W, q = i / W, f = q / R2, n2 = q - f * R2;
+        const cplx* p = lds_dyn + (f * N + n2) * W + c;
+        cplx v[R1];
+#pragma unroll
+        for (int k = 0; k < R1; ++k) v[k] = p[k * R2 * W];
+        twiddle_all<R1, true>(v, tw, n2);
+        dft<R1, true>(v);
+        cplx* o = base + f * plane + (size_t)n2 * cs + c;
+#pragma unroll
+        for (int k = 0; k < R1; ++k) st_wt(o + (size_t)k * R2 * cs, v[k]);
+    }
 }
 
 // ----------------------------------------------------- launch helpers ----
@@ -542,6 +626,29 @@ inline hipError_t cols_launch(cplx* data, const ProbDev& pd, int W, const SysSta
     hipLaunchKernelGGL((k_cols<N, P, MODE, SEQ, NT>), dim3(blocks), dim3(g.threads), g.lds, s, data, pd, W,
                        st, tw);
     return hipGetLastError();
+}
+
+// The sweep pass on tiles of W columns, W from {4, 8, 16}: blocks as wide as
+// the tiles while three of them fit in LDS, else half as wide (384 points on
+// 16-column tiles, 384^2 x 16: 16.5 us by 8 columns, 24.9 by 16).
+template <int N>
+inline hipError_t cols_sweep_launch(cplx* data, const ProbDev& pd, int W, const SysState* st, const cplx* tw,
+                                    hipStream_t s) {
+    using C = ColSweep<N>;
+    while (W > 4 && (size_t)2 * N * W * sizeof(cplx) > kMaxLds / 3) W /= 2;
+    const size_t lds = (size_t)2 * N * W * sizeof(cplx);
+    const int items = std::max(2 * C::R2, C::R1) * W;
+    const int threads = std::min(512, (items + 63) / 64 * 64);
+    auto go = [&](auto kernel) -> hipError_t {
+        hipError_t e = allow_lds(kernel, lds);
+        if (e != hipSuccess) return e;
+        hipLaunchKernelGGL(kernel, dim3(pd.nsys * (pd.nx / W)), dim3(threads), lds, s, data, pd, st, tw);
+        return hipGetLastError();
+    };
+    if (W == 4) return go(k_cols_sweep<N, 4>);
+    if (W == 8) return go(k_cols_sweep<N, 8>);
+    if (W == 16) return go(k_cols_sweep<N, 16>);
+    return hipErrorInvalidValue;
 }
 
 // The LDS-twiddle pass: W from {4, 8, 16} as a template parameter.

@@ -178,3 +178,27 @@ def test_lds_twiddle_column_solves_match_oracle_and_plain(nx, nz):
         assert max(errs) < 1e-4, (c, errs)
         plain = plan.solve(u0, rtol=1e-6, maxit=500, plain=True)
         assert torch.equal(res.x, plain.x) and np.array_equal(res.iters, plain.iters), c
+
+
+@pytest.mark.parametrize("precision,tol", [("c64", KERNEL_TOL), ("c128", 1e-12)])
+@pytest.mark.parametrize("nx,nz", [(48, 16), (24, 24), (48, 32), (64, 48), (24, 64), (32, 128), (48, 192), (32, 384),
+                                   (48, 256), (64, 512)])
+def test_default_column_pass_lengths(nx, nz, precision, tol):
+    """The default column variant at every length with its own pass, on tiles
+    of 16 and (nx = 24) 8 columns and narrower, both symbols, against the
+    oracle."""
+    from paper_2402_02116_amd.plan import Plan
+    print(f"default columns {nx}x{nz} {precision}", flush=True)
+    for symbol in ("spectral", "central"):
+        p, maps = _case(nx, nz, 3)
+        plan = Plan([dict(p, symbol=symbol)], precision=precision)
+        plan.set_contrast(0, maps)
+        rng = np.random.default_rng(13)
+        u = W.round_f32(rng.standard_normal((3, 2, nz, nx)) + 1j * rng.standard_normal((3, 2, nz, nx)))
+        ut = plan.pack([u])
+        ref = LSProblem(nx, nz, 8.0, p["c0"], p["rho0"], p["freq_hz"], 0.02, maps, symbol=symbol).apply(u)
+        width = plan.tuning(0)["col_width"]
+        for w in (width, 8, 4):
+            plan.set_tuning(0, col_width=w)
+            out = plan.view(plan.apply(ut), 0).cpu().numpy().astype(np.complex128)
+            assert _rel(out, ref) < tol, (symbol, w)
