@@ -264,7 +264,7 @@ def _pass_instance(k, tuning, n=256):
             return f"fw::c64::(anonymous namespace)::k_srows<{n}, {p}, 0, {512 if n >= 384 and n // p <= 32 else 256}>"
         if tuning.get("stencil_sys") == -1:   # the z-marching stencil
             return f"fw::c64::k_body_force_z<64, {tuning['stencil_rows']}, 0>"
-        return f"fw::c64::k_body_force<64, {tuning['stencil_rows']}, 0>"
+        return f"fw::c64::k_body_force<64, {tuning['stencil_rows']}>"
     if k == 1:
         return f"fw::c64::k_rows<{n}, {tuning['row_points']}, false, 0>"
     if k == 2:

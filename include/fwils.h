@@ -486,9 +486,10 @@ typedef struct {
     int32_t stencil_rows;  /* contrast-stencil tile height: 4, 8 or 16 (with
                               stencil_sys = -1: rows per step, 4 or 8; complex128
                               plans 4) */
-    int32_t stencil_sys;   /* systems per stencil workgroup, 0 = from the grid size (the
-                              plain stencil; the Krylov update modes always take the
-                              count from the grid size); -1 = the z-marching stencil
+    int32_t stencil_sys;   /* systems per stencil workgroup of the plain stencil
+                              (the Krylov updates are then a pass of their own), 0 =
+                              the library's choice from the grid size and system
+                              count, the z-marching stencil for large ones; -1 = the z-marching stencil
                               (one system per workgroup walking a column strip down a
                               range of rows, every mode) */
     int32_t fused_points;  /* 0: contrast stencil and forward row transform as two

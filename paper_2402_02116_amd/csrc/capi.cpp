@@ -92,6 +92,7 @@ struct ProbHost {
     int np_gm;            // ... from its GMRES epilogues
     int np_vec;           // partial records per system from vector kernels
     KernelCfg cfg;        // kernel variants (defaults, the autotuner's or the caller's)
+    StCfg st_run;         // the stencil variant that cfg.st stands for at this problem's size
     float tuned_us[4];    // autotune: stencil, row, column, stencil + rows time of the choice
     // dimensions of the field (2-D: ny = 1, two components, five maps)
     bool d3 = false;      // a 3-D problem (fwils_plan_create3)
@@ -283,7 +284,7 @@ hipError_t inverse_pass(fwils_plan pl, const ProbHost& P, const ProbDev& d, int 
 // The contrast stencil of either dimension (vector update vm, a.b the output).
 hipError_t stencil_any(const ProbHost& P, const ProbDev& d, int vm, const StencilArgs& a, SysState* st, hipStream_t s) {
     if (P.d3) return launch_stencil3(vm, a, view3(P, d), st, s);
-    return launch_stencil(vm, P.cfg.st, a, d, st, s);
+    return launch_stencil(vm, P.st_run, a, d, st, s);
 }
 
 // y = G0 conv f for problem P (f read, out written; tmp is scratch).
@@ -831,6 +832,7 @@ void layout_plan(fwils_plan pl) {
         P.nrec = 0;
         P.tuned_us[0] = P.tuned_us[1] = P.tuned_us[2] = P.tuned_us[3] = 0.f;
         P.np_gm = P.np_rows = row_geom(P.p.nx, P.cfg.row_pi, P.rps).blocks_per_sys;   // the inverse pass's partials
+        P.st_run = st_resolve(P.p.nx, P.p.nz, P.p.nsys, P.cfg.st);
         P.planes = P.d3 && plane_size_ok(P.p.nx, P.ny);
         if (P.planes) P.np_rows = P.rps / P.ny / plane_geom(P.p.nx, P.ny, P.rps / P.ny).G;
         P.np_vec = vec_blocks_per_sys((int)P.n_per_sys);
@@ -1931,7 +1933,7 @@ fwils_status fwils_apply_pass(fwils_plan plan, int32_t pass, const void* u, void
                     const StencilArgs a{at(u, P), nullptr, nullptr, nullptr, nullptr, maps_at(plan, P), nullptr, 0};
                     FW_HIP(launch_srows(0, P.cfg.fuse_p, a, tmp, P.dev, nullptr, plan->tw, s));
                 } else {
-                    FW_HIP(launch_body_force(P.cfg.st, at(u, P), at(plan->tmp2, P), maps_at(plan, P), P.dev, nullptr, s));
+                    FW_HIP(launch_body_force(P.st_run, at(u, P), at(plan->tmp2, P), maps_at(plan, P), P.dev, nullptr, s));
                 }
                 break;
             case 1:   // part of pass 0 when the stencil and the rows are fused
@@ -2288,6 +2290,7 @@ bool cfg_ok(const ProbHost& P, const KernelCfg& k) {
 
 void apply_cfg(fwils_plan pl, ProbHost& P, const KernelCfg& k) {
     P.cfg = k;
+    P.st_run = st_resolve(P.p.nx, P.p.nz, P.p.nsys, k.st);
     P.dev.tile_sh = col_tile_shift(P.p.nx, k.col.W);   // the spectrum follows the column blocks
     P.np_gm = P.np_rows = row_geom(P.p.nx, k.row_pi, 2 * P.p.nz).blocks_per_sys;
     drop_graphs(pl);
@@ -2350,7 +2353,8 @@ hipError_t tune_launch(fwils_plan pl, const ProbHost& P, int kind, const KernelC
         return launch_rows_inv(P.p.nx, k.row_pi, EPI_BICG_V, tmp, u, at(pl->rhat, P), at(pl->v, P),
                                part_at(pl->partV, pl, P), rows, 2 * P.p.nz, tile_rows(P.dev), nullptr, pl->tw,
                                pl->stream);
-    if (kind == FWILS_TUNE_STENCIL) return launch_body_force(k.st, u, tmp, maps_at(pl, P), P.dev, nullptr, pl->stream);
+    const StCfg sv = st_resolve(P.p.nx, P.p.nz, P.p.nsys, k.st);
+    if (kind == FWILS_TUNE_STENCIL) return launch_body_force(sv, u, tmp, maps_at(pl, P), P.dev, nullptr, pl->stream);
     cplx* tmp2 = at(pl->tmp2, P);
     if (kind == FWILS_TUNE_ROWS)
         return launch_rows_fwd(P.p.nx, k.row_p, tmp2, tmp, rows, 2 * P.p.nz, tile_rows(P.dev), nullptr, pl->tw,
@@ -2361,7 +2365,7 @@ hipError_t tune_launch(fwils_plan pl, const ProbHost& P, int kind, const KernelC
             const StencilArgs a{u, nullptr, nullptr, nullptr, nullptr, maps_at(pl, P), nullptr, 0};
             return launch_srows(0, k.fuse_p, a, tmp, P.dev, nullptr, pl->tw, pl->stream);
         }
-        hipError_t e = launch_body_force(k.st, u, tmp2, maps_at(pl, P), P.dev, nullptr, pl->stream);
+        hipError_t e = launch_body_force(sv, u, tmp2, maps_at(pl, P), P.dev, nullptr, pl->stream);
         if (e == hipSuccess)
             e = launch_rows_fwd(P.p.nx, k.row_p, tmp2, tmp, rows, 2 * P.p.nz, tile_rows(P.dev), nullptr, pl->tw,
                                 pl->stream);

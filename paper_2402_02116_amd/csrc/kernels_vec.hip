@@ -29,24 +29,13 @@ constexpr int STX = 64, STZ = 8;
 
 __device__ __forceinline__ int wrap(int i, int n) { return i < 0 ? i + n : (i >= n ? i - n : i); }
 
-// The vector update of the input (StencilVec, bicg.h) is written for the
-// tile's own cells and used (halo included) as the stencil's input.  p is
-// double-buffered by the caller because neighbouring tiles read p_old in
-// their halos.
-
-template <int TX, int TZ, int VM>
-__global__ __launch_bounds__(256) void k_body_force(const cplx* __restrict__ u,
-                                                    const cplx* __restrict__ a1,
-                                                    const cplx* __restrict__ a2,
-                                                    cplx* __restrict__ wout,
-                                                    cplx* __restrict__ b,
-                                                    const real* __restrict__ maps, ProbDev pd,
-                                                    int S, SysState* __restrict__ st,
-                                                    const double* __restrict__ part, int np,
-                                                    cplx* __restrict__ rhat,
-                                                    const cplx* __restrict__ a3,
-                                                    cplx* __restrict__ xio,
-                                                    cplx* __restrict__ rout) {
+// The BiCGSTAB updates of the input run before it as a streaming pass
+// (launch_bicg_update): fused into the tiles' loads they read their vectors
+// again in the halos.
+template <int TX, int TZ>
+__global__ __launch_bounds__(256) void k_body_force(const cplx* __restrict__ u, cplx* __restrict__ b,
+                                                    const real* __restrict__ maps, ProbDev pd, int S,
+                                                    const SysState* __restrict__ st) {
     static_assert(TX <= 64 && TZ % 4 == 0, "tile");
     constexpr int HX = TX + 4, HZ = TZ + 4, SX = TX + 2, SZ = TZ + 2;
     constexpr int KS = (SZ + 3) / 4;     // stress rows per thread
@@ -54,7 +43,6 @@ __global__ __launch_bounds__(256) void k_body_force(const cplx* __restrict__ u,
     constexpr int KH = HZ / 4;           // displacement rows per thread
     __shared__ cplx su[2][HZ][HX];
     __shared__ cplx ss[3][SZ][SX];
-    __shared__ double red[4 * kPartialNV];
     const int nx = pd.nx, nz = pd.nz;
     const size_t plane = (size_t)nx * nz;
     const int ntx = nx / TX;
@@ -92,96 +80,23 @@ __global__ __launch_bounds__(256) void k_body_force(const cplx* __restrict__ u,
 
     const real sc = pd.inv4dx2;
     for (int sys = sys0; sys < sys0 + S && sys < pd.nsys; ++sys) {
-        if (st != nullptr) {   // uniform over the block
-            const int stw = st[sys].status;
-            if constexpr (VM == VM_PX) {
-                if (!closing_enters(stw, kStampPx)) continue;
-            } else {
-                if (stw != ST_RUNNING) {
-                    // the iteration's closing kernel is done: drop its tag
-                    if (VM == VM_S && st_tag(stw) != 0 && tile == 0 && threadIdx.x == 0)
-                        st[sys].status = st_code(stw);
-                    continue;
-                }
-            }
-        }
-        cplx c1 = mkc(0.f, 0.f), c2 = mkc(0.f, 0.f), c3 = mkc(0.f, 0.f);
-        bool fresh = false;
-        int step = SS_FULL;
-        if constexpr (VM != VM_NONE) {
-            step = stencil_scalars<VM>(st, sys, part, np, red, tile == 0 && threadIdx.x == 0, c1, c2, c3, fresh);
-            if (step == SS_SKIP) continue;
-        }
+        if (st != nullptr && st[sys].status != ST_RUNNING) continue;   // uniform over the block
         const size_t so = (size_t)sys * 2 * plane;
+        const cplx* us = u + so;
         cplx* bs = b + so;
-        // VM_PX on an own cell: r = s - omega t, x += alpha p_old + omega s
-        auto close_iteration = [&](size_t gi) {
-            const cplx sv = u[so + gi], tv = a3[so + gi], pv = a1[so + gi];
-            const cplx rv = close_r(sv, tv, c2);
-            st_wt(rout + so + gi, rv);
-            st_wt(xio + so + gi, close_x(xio[so + gi], pv, sv, c3, c2));
-            if (fresh) rhat[so + gi] = rv;
-        };
-        if constexpr (VM == VM_PX) {
-            if (step == SS_XONLY) {   // stopped: the last solution update only
-                if (lane) {
-#pragma unroll
-                    for (int k = 0; k < KB; ++k) {
-                        const size_t gi = (size_t)(z0 + tg + 4 * k) * nx + x0 + tx;
-                        close_iteration(gi);
-                        close_iteration(plane + gi);
-                    }
-                }
-                continue;
-            }
-        }
-        // input field value at global index gi of this system (comp offset included)
-        auto field = [&](size_t gi) -> cplx {
-            if constexpr (VM == VM_NONE) {
-                return u[so + gi];
-            } else if constexpr (VM == VM_P) {
-                const cplx rv = u[so + gi];
-                if (fresh) return rv;
-                const cplx pv = a1[so + gi], vv = a2[so + gi];
-                return cadd(rv, cmul(c1, csub(pv, cmul(c2, vv))));
-            } else if constexpr (VM == VM_PX) {
-                const cplx rv = close_r(u[so + gi], a3[so + gi], c2);
-                if (fresh) return rv;
-                const cplx pv = a1[so + gi], vv = a2[so + gi];
-                return cadd(rv, cmul(c1, csub(pv, cmul(c2, vv))));
-            } else {
-                return csub(u[so + gi], cmul(c1, a1[so + gi]));
-            }
-        };
         __syncthreads();   // previous system's reads of su / ss are done
 #pragma unroll
         for (int k = 0; k < KH; ++k) {
             const int hz = tg + 4 * k;
             const size_t row = (size_t)wrap(z0 - 2 + hz, nz) * nx;
             if (lane) {
-                const cplx f0 = field(row + x0 + tx), f1 = field(plane + row + x0 + tx);
-                su[0][hz][tx + 2] = f0;
-                su[1][hz][tx + 2] = f1;
-                if constexpr (VM != VM_NONE) {
-                    if (hz >= 2 && hz < TZ + 2) {     // the tile's own cells
-                        st_wt(wout + so + row + x0 + tx, f0);
-                        st_wt(wout + so + plane + row + x0 + tx, f1);
-                        if constexpr (VM == VM_P) {
-                            if (fresh) {              // p = r here
-                                rhat[so + row + x0 + tx] = f0;
-                                rhat[so + plane + row + x0 + tx] = f1;
-                            }
-                        } else if constexpr (VM == VM_PX) {
-                            close_iteration(row + x0 + tx);
-                            close_iteration(plane + row + x0 + tx);
-                        }
-                    }
-                }
+                su[0][hz][tx + 2] = us[row + x0 + tx];
+                su[1][hz][tx + 2] = us[plane + row + x0 + tx];
             }
             if (tx < 4) {
                 const int gx = wrap(x0 - 2 + hux, nx);
-                su[0][hz][hux] = field(row + gx);
-                su[1][hz][hux] = field(plane + row + gx);
+                su[0][hz][hux] = us[row + gx];
+                su[1][hz][hux] = us[plane + row + gx];
             }
         }
         __syncthreads();
@@ -588,6 +503,15 @@ bool st_cfg_ok(int nx, int nz, const StCfg& c) {
     return c.S == 0 || c.S == 1 || c.S == 2 || c.S == 4 || c.S == 8 || c.S == 16;
 }
 
+StCfg st_resolve(int nx, int nz, int nsys, const StCfg& c) {
+#ifndef FW_C128
+    const long long n = (long long)nx * nz * nsys;
+    if (c.S == 0 && n >= (1LL << 21) && st_cfg_ok(nx, nz, StCfg{4, kStMarch}))
+        return StCfg{4, n >= (1LL << 22) ? kStMarch : kStMarchSplit};
+#endif
+    return c;
+}
+
 int st_candidates(int nx, int nz, StCfg* out, int cap) {
     int k = 0;
     const int tzs[3] = {8, 4, 16};
@@ -628,10 +552,6 @@ __global__ __launch_bounds__(256) void k_bicg_update(const cplx* __restrict__ u,
             return;
         }
     }
-    cplx c1 = mkc(0.f, 0.f), c2 = mkc(0.f, 0.f), c3 = mkc(0.f, 0.f);
-    bool fresh = false;
-    const int step = stencil_scalars<VM>(st, sys, part, np, red, bi == 0 && t == 0, c1, c2, c3, fresh);
-    if (step == SS_SKIP) return;
     const size_t so = (size_t)sys * n;
     const cplx* __restrict__ us = u + so;
     const cplx* __restrict__ a1s = a1 + so;
@@ -643,8 +563,8 @@ __global__ __launch_bounds__(256) void k_bicg_update(const cplx* __restrict__ u,
     cplx* __restrict__ ros = rout + so;
     constexpr int U = 4;   // elements per thread in flight
     const int stride = bps * 256;
-    for (int i0 = bi * 256 + t; i0 < n; i0 += U * stride) {
-        cplx r0[U], r1[U], r2[U], r3[U], xv[U];
+    cplx r0[U], r1[U], r2[U], r3[U], xv[U];
+    auto load = [&](int i0) {
 #pragma unroll
         for (int k = 0; k < U; ++k) {
             const int i = i0 + k * stride;
@@ -656,13 +576,23 @@ __global__ __launch_bounds__(256) void k_bicg_update(const cplx* __restrict__ u,
                 } else if constexpr (VM == VM_PX) {
                     r1[k] = a3s[i];
                     r2[k] = a1s[i];
-                    if (step == SS_FULL) r3[k] = a2s[i];
+                    r3[k] = a2s[i];
                     xv[k] = xs[i];
                 } else if constexpr (VM == VM_S) {
                     r1[k] = a1s[i];
                 }
             }
         }
+    };
+    // the first elements travel while the scalars are formed from the records
+    // (192 x 48 x 48, update, stencil and rows: 26.5 -> 24.9 us)
+    load(bi * 256 + t);
+    cplx c1 = mkc(0.f, 0.f), c2 = mkc(0.f, 0.f), c3 = mkc(0.f, 0.f);
+    bool fresh = false;
+    const int step = stencil_scalars<VM>(st, sys, part, np, red, bi == 0 && t == 0, c1, c2, c3, fresh);
+    if (step == SS_SKIP) return;
+    for (int i0 = bi * 256 + t; i0 < n; i0 += U * stride) {
+        if (i0 >= U * stride) load(i0);
 #pragma unroll
         for (int k = 0; k < U; ++k) {
             const int i = i0 + k * stride;
@@ -733,19 +663,11 @@ static void body_force_z_launch(const StencilArgs& a, const ProbDev& pd, SysStat
                        a.wout, a.b, a.maps, pd, zr, st, a.part, a.np, a.rhat, a.a3, a.xio, a.rout, sg);
 }
 
-template <int TX, int TZ, int VM>
-static hipError_t body_force_launch(const StCfg& c, const StencilArgs& a, const ProbDev& pd, SysState* st,
+template <int TX, int TZ>
+static hipError_t body_force_launch(const StCfg& c, const StencilArgs& a, const ProbDev& pd, const SysState* st,
                                     hipStream_t s) {
-    if constexpr (TZ == 4 || TZ == 8) {
-        if (c.S == kStMarch) {
-            body_force_z_launch<TX, TZ, VM>(a, pd, st, s);
-            return hipGetLastError();
-        }
-    }
     const int ntiles = (pd.nx / TX) * (pd.nz / TZ);
-    // the solver's update modes carry two to five vectors per system and take
-    // the automatic count (the tuned count is timed in the plain mode)
-    int S = VM == VM_NONE ? c.S : 0;
+    int S = c.S;
     if (S == 0) {
         // several systems per block once there are plenty of blocks
         S = 1;
@@ -753,18 +675,24 @@ static hipError_t body_force_launch(const StCfg& c, const StencilArgs& a, const 
     }
     S = std::min(S, std::max(pd.nsys, 1));
     const int blocks = ntiles * ((pd.nsys + S - 1) / S);
-    hipLaunchKernelGGL((k_body_force<TX, TZ, VM>), dim3(blocks), dim3(256), 0, s, a.u, a.a1, a.a2, a.wout,
-                       a.b, a.maps, pd, S, st, a.part, a.np, a.rhat, a.a3, a.xio, a.rout);
+    hipLaunchKernelGGL((k_body_force<TX, TZ>), dim3(blocks), dim3(256), 0, s, a.u, a.b, a.maps, pd, S, st);
     return hipGetLastError();
 }
 
 template <int TX, int TZ>
 static hipError_t body_force_vm(int vm, const StCfg& c, const StencilArgs& a, const ProbDev& pd, SysState* st,
                                 hipStream_t s) {
-    if (vm == VM_NONE) return body_force_launch<TX, TZ, VM_NONE>(c, a, pd, st, s);
-    if (vm == VM_P) return body_force_launch<TX, TZ, VM_P>(c, a, pd, st, s);
-    if (vm == VM_PX) return body_force_launch<TX, TZ, VM_PX>(c, a, pd, st, s);
-    return body_force_launch<TX, TZ, VM_S>(c, a, pd, st, s);
+    if constexpr (TZ == 4 || TZ == 8) {
+        if (c.S == kStMarch) {
+            if (vm == VM_NONE) body_force_z_launch<TX, TZ, VM_NONE>(a, pd, st, s);
+            else if (vm == VM_P) body_force_z_launch<TX, TZ, VM_P>(a, pd, st, s);
+            else if (vm == VM_PX) body_force_z_launch<TX, TZ, VM_PX>(a, pd, st, s);
+            else body_force_z_launch<TX, TZ, VM_S>(a, pd, st, s);
+            return hipGetLastError();
+        }
+    }
+    if (vm != VM_NONE) return hipErrorInvalidValue;   // the update is a pass of its own
+    return body_force_launch<TX, TZ>(c, a, pd, st, s);
 }
 
 template <int TX>
@@ -777,17 +705,31 @@ static hipError_t body_force_tz(int vm, const StCfg& c, const StencilArgs& a, co
     return body_force_vm<TX, 8>(vm, c, a, pd, st, s);
 }
 
-hipError_t launch_stencil(int vm, const StCfg& c, const StencilArgs& a, const ProbDev& pd, SysState* st,
+hipError_t launch_stencil(int vm, const StCfg& cfg, const StencilArgs& a, const ProbDev& pd, SysState* st,
                           hipStream_t s) {
+    const StCfg c{cfg.TZ, cfg.S == kStMarchSplit ? kStMarch : cfg.S};
     if (!st_cfg_ok(pd.nx, pd.nz, c) || vm < 0 || vm > 3 || (vm != 0 && !st) || ((vm == VM_P || vm == VM_PX) && !a.rhat) ||
-        (vm == VM_PX && (!a.a3 || !a.xio || !a.rout)))
+        (vm == VM_PX && (!a.a3 || !a.xio || !a.rout)) || (vm != VM_NONE && !a.wout))
         return hipErrorInvalidValue;
+    StencilArgs p = a;
+    if (vm != VM_NONE && cfg.S != kStMarch) {
+        // Tiles read one to four vectors of an update again in their halo rows
+        // and hold one or two wavefronts per SIMD with it: the update runs as
+        // a streaming pass of its own, then the plain stencil on its result
+        // (direction update, stencil and rows: 512^2 x 32 615 -> 352 us,
+        // 384^2 x 16 165 -> 90, 256^2 x 16 60 -> 43, 192 x 48 x 48 37 -> 25,
+        // 96 x 64 x 1 18.2 -> 16.4).
+        const hipError_t e = launch_bicg_update(vm, a, 2LL * pd.nx * pd.nz, pd.nsys, st, s);
+        if (e != hipSuccess) return e;
+        p.u = a.wout;
+        vm = VM_NONE;
+    }
     switch (tile_x(pd.nx)) {
-        case 64: return body_force_tz<64>(vm, c, a, pd, st, s);
-        case 48: return body_force_tz<48>(vm, c, a, pd, st, s);
-        case 32: return body_force_tz<32>(vm, c, a, pd, st, s);
-        case 24: return body_force_tz<24>(vm, c, a, pd, st, s);
-        case 16: return body_force_tz<16>(vm, c, a, pd, st, s);
+        case 64: return body_force_tz<64>(vm, c, p, pd, st, s);
+        case 48: return body_force_tz<48>(vm, c, p, pd, st, s);
+        case 32: return body_force_tz<32>(vm, c, p, pd, st, s);
+        case 24: return body_force_tz<24>(vm, c, p, pd, st, s);
+        case 16: return body_force_tz<16>(vm, c, p, pd, st, s);
         default: return hipErrorInvalidValue;
     }
 }

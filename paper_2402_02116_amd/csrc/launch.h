@@ -50,6 +50,18 @@ struct StCfg {
                // z-marching kernel (one system per block)
 };
 constexpr int kStMarch = -1;
+// The variant that runs for c on a problem of nsys systems.  S = 0 leaves the
+// choice to the grid size (complex64): the z-marching kernel by 4-row steps
+// with the solver's updates fused into it from 2^22 cell-systems on, the plain
+// z-marching kernel after a separate update (kStMarchSplit) from 2^21 on, else
+// tiles after a separate update (StCfg{TZ, 0}).  Decided from the problem's
+// systems, not a view's, so that a system's results do not depend on the
+// batch it is launched in.  Measured per iteration of 24 (update + stencil +
+// rows in brackets): 512^2 x 32 863 us marching (330), 946 tiles (351);
+// 1024^2 x 4 540 (200), 551 (210); 512^2 x 8 251 (85), 245 (79); plain stencil
+// 384^2 x 16 20.7 us marching, 24.0 tiles; 256^2 x 16 13.1, 12.0.
+constexpr int kStMarchSplit = -2;
+StCfg st_resolve(int nx, int nz, int nsys, const StCfg& c);
 struct KernelCfg {
     int row_p;   // forward row-transform points per thread
     int row_pi;  // inverse row-transform points per thread (its epilogues hold more registers)
