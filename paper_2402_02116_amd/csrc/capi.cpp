@@ -924,6 +924,12 @@ ProbDev3 make_dev3(const fwils_problem3& p) {
         }
     }
     d.ga = mkc((real)(1.0 - eta * eta), (real)(2.0 * eta));
+    // orthotropic (VTI included): squares in the diagonal entries, its own
+    // product in each of the others
+    d.ortho = 1;
+    for (int a = 0; a < 6; ++a)
+        for (int b = 0; b < 6; ++b)
+            if (d.gq[a][b] != (real)0 && !(a < 3 ? b < 3 : b == a)) d.ortho = 0;
     d.gscale = (real)(1.0 / (rw2 * (double)p.nx * (double)p.ny * (double)p.nz));
     d.dk[0] = (real)(2.0 * M_PI / (p.nx * p.dx));
     d.dk[1] = (real)(2.0 * M_PI / (p.ny * p.dx));

@@ -768,9 +768,8 @@ __global__ __launch_bounds__(256) void k_axis(cplx* __restrict__ data, int S, in
 //      inverse butterflies;
 //   3. sweep 1 undone, to memory.
 // Small radices in sweep 2 keep the three components of an item in few
-// registers.  Along a column the six entries of Gamma' are quadratic in kz,
-// with coefficients formed once per column (36 -> 12 multiply-adds per
-// wavenumber).  Against all points of three components in one thread
+// registers.  The terms of Gamma' without kz are formed once per column.
+// Against all points of three components in one thread
 // (two wavefronts per SIMD at 12 points): 32 points at 80 x 40 x 100 90 -> 83
 // us (a read and a write of the field at the rate of a large copy take 96,
 // part of it stays in the memory-side cache), 48 points at 96 x 64 x 7 35.5 ->
@@ -829,21 +828,38 @@ __global__ __launch_bounds__(kGreenThreads) void k_green3(cplx* __restrict__ dat
         // products of two different components: 0 at an even axis's Nyquist index
         const real kxo = (pd.nx % 2 == 0 && ix == pd.nx / 2) ? 0.f : kx;
         const real kyo = (pd.ny % 2 == 0 && iy == pd.ny / 2) ? 0.f : ky;
-        real g0[6], g1[6];   // Gamma'_p = g0 + g1 kzo + gq kz^2
+        // The entries are summed in the order of mono, so that their rounding
+        // (which a wavenumber near the slowness surface amplifies) does not
+        // depend on the path: terms of a column that are the same for all of
+        // its wavenumbers first, then those in kz; an orthotropic medium has
+        // the latter in five entries only.
+        const real kx2 = kx * kx, ky2 = ky * ky, kxy = kxo * kyo;
+        real g0[6];
 #pragma unroll
-        for (int e = 0; e < 6; ++e) {
-            g0[e] = pd.gq[e][0] * (kx * kx) + pd.gq[e][1] * (ky * ky) + pd.gq[e][5] * (kxo * kyo);
-            g1[e] = pd.gq[e][3] * kyo + pd.gq[e][4] * kxo;
-        }
+        for (int e = 0; e < 6; ++e) g0[e] = pd.gq[e][0] * kx2 + pd.gq[e][1] * ky2;
 #pragma unroll
         for (int k = 0; k < R2; ++k) {
             const int iz = k1 + R1 * k;
             const real kz = axis_k(iz, N, pd.dk[2], pd.dx, central);
             const real kzo = (N % 2 == 0 && iz == N / 2) ? 0.f : kz;
-            const real kz2 = kz * kz;
+            const real kz2 = kz * kz, kyz = kyo * kzo, kxz = kxo * kzo;
             real g[6];
+            if (pd.ortho) {
 #pragma unroll
-            for (int e = 0; e < 6; ++e) g[e] = g0[e] + (g1[e] * kzo + pd.gq[e][2] * kz2);
+                for (int e = 0; e < 3; ++e) g[e] = g0[e] + pd.gq[e][2] * kz2;
+                g[3] = pd.gq[3][3] * kyz;
+                g[4] = pd.gq[4][4] * kxz;
+                g[5] = pd.gq[5][5] * kxy;
+            } else {
+#pragma unroll
+                for (int e = 0; e < 6; ++e) {
+                    real a = g0[e] + pd.gq[e][2] * kz2;
+                    a += pd.gq[e][3] * kyz;
+                    a += pd.gq[e][4] * kxz;
+                    a += pd.gq[e][5] * kxy;
+                    g[e] = a;
+                }
+            }
             cplx b3[3] = {v[0][k], v[1][k], v[2][k]};
             green_mul3(b3, g, pd.ga, pd.gscale);
             v[0][k] = b3[0];

@@ -192,6 +192,7 @@ struct ProbDev3 {
     // entry Gamma'_p, p in (xx, yy, zz, yz, xz, xy), is sum_q gq[p][q] mono_q
     // with mono = (kx^2, ky^2, kz^2, ky kz, kx kz, kx ky)
     real gq[6][6];
+    int ortho;            // gq has no terms but those of an orthotropic medium
     cplx ga;              // (1 + i eta)^2
     real gscale;          // 1 / (rho0 w^2 nx ny nz)
     real dk[3];           // 2 pi / (n dx) per axis
