@@ -818,6 +818,21 @@ fwils_status check_field_ptrs(std::initializer_list<const void*> ptrs) {
     return FWILS_OK;
 }
 
+bool fuse_ok(const ProbHost& P, int fp);
+
+// The fused stencil + rows kernel a new problem starts with: rows of up to 256
+// points, by 8 points per thread below 2^19 cell-systems (more, smaller blocks)
+// and 16 from there on (12 for 3 2^k).  One BiCGSTAB iteration, separate ->
+// fused: 96 x 64 x 1 56 -> 52 us, 128^2 x 16 87 -> 73 (16 points: 84), 192 x 48
+// x 48 104 -> 93, 192^2 x 64 258 -> 229, 256^2 x 4 75 -> 67 (76), 256^2 x 16
+// 130 -> 109 (8 points: 119).  Longer rows leave a block few rows of its own
+// beside its halo rows: 512^2 x 32 848 -> 856 us.
+int fuse_default(const ProbHost& P) {
+    if (P.p.nx > 256) return 0;
+    const int fp = P.p.nx % 3 == 0 ? 12 : (long long)P.p.nsys * (long long)P.cells < (1LL << 19) ? 8 : 16;
+    return fuse_ok(P, fp) ? fp : 0;
+}
+
 // Offsets of every problem in the plan-level vectors, partial-record sizes
 // and the workspace layout, from the problems' dimensions and variants.
 void layout_plan(fwils_plan pl) {
@@ -1006,6 +1021,7 @@ fwils_status fwils_plan_create(const fwils_problem* probs, int32_t nprob, fwils_
         P.cells = (size_t)P.p.nz * P.p.nx;
         P.rps = 2 * P.p.nz;
         P.cfg = kernel_cfg_default(P.p.nx, P.p.nz);
+        P.cfg.fuse_p = fuse_default(P);
         P.dev.tile_sh = col_tile_shift(P.p.nx, P.cfg.col.W);
         pl->probs.push_back(P);
     }

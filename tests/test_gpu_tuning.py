@@ -202,3 +202,27 @@ def test_default_column_pass_lengths(nx, nz, precision, tol):
             plan.set_tuning(0, col_width=w)
             out = plan.view(plan.apply(ut), 0).cpu().numpy().astype(np.complex128)
             assert _rel(out, ref) < tol, (symbol, w)
+
+
+@pytest.mark.parametrize("nx,nz,nsys", [(16, 16, 1), (24, 16, 1), (48, 24, 3), (192, 24, 2), (256, 16, 1), (256, 256, 7),
+                                        (256, 256, 8), (384, 16, 2)])
+def test_default_fused_rows(nx, nz, nsys):
+    """The variant a new problem starts with, on either side of each edge of
+    its rule, against the separate stencil and rows and the oracle."""
+    from paper_2402_02116_amd.plan import Plan
+    print(f"default fused rows {nx}x{nz} x {nsys}", flush=True)
+    p, maps = _case(nx, nz, nsys)
+    plan = Plan([p])
+    plan.set_contrast(0, maps)
+    fp = plan.tuning(0)["fused_points"]
+    assert (fp != 0) <= (nx <= 256) and fp in (0, 8, 12, 16)
+    rng = np.random.default_rng(17)
+    u = W.round_f32(rng.standard_normal((nsys, 2, nz, nx)) + 1j * rng.standard_normal((nsys, 2, nz, nx)))
+    ut = plan.pack([u])
+    out = plan.view(plan.apply(ut), 0).cpu().numpy().astype(np.complex128)
+    plan.set_tuning(0, fused_points=0)
+    sep = plan.view(plan.apply(ut), 0).cpu().numpy().astype(np.complex128)
+    ref = LSProblem(nx, nz, 8.0, p["c0"], p["rho0"], p["freq_hz"], 0.02, maps).apply(u[-1:])
+    # each side is within the bound of the exact result
+    assert _rel(out, sep) < 2 * KERNEL_TOL
+    assert _rel(out[-1:], ref) < KERNEL_TOL
