@@ -680,12 +680,10 @@ hipError_t gm_cycle(fwils_plan pl, const ProbHost& P, const cplx* b, double rtol
         cplx* wn = a.V + (size_t)(j + 1) * a.vstride;
         e = matvec(pl, P, P.dev, wj, at(pl->tmp, P), maps_at(pl, P), EPI_ARNOLDI, nullptr, wn, nullptr, a.st, s,
                    &ge);
-        if (e == hipSuccess) e = launch_gm_sum(a, GM_SUM_PROJ1, P.np_gm, j, cgs2, rtol, false, s);
-        if (e == hipSuccess) e = launch_gm_update(a, j, 1, !cgs2, s);
+        if (e == hipSuccess) e = launch_gm_update(a, j, 1, P.np_gm, !cgs2, s);
         if (cgs2) {
             if (e == hipSuccess) e = launch_gm_dots(a, j, s);
-            if (e == hipSuccess) e = launch_gm_sum(a, GM_SUM_PROJ2, nbv, j, cgs2, rtol, false, s);
-            if (e == hipSuccess) e = launch_gm_update(a, j, 2, true, s);
+            if (e == hipSuccess) e = launch_gm_update(a, j, 2, nbv, true, s);
         }
         if (e == hipSuccess) e = launch_gm_sum(a, GM_SUM_HESS, nbv, j, cgs2, rtol, false, s);
     }
@@ -2108,7 +2106,7 @@ fwils_status fwils_time_gmres_pass(fwils_plan plan, int32_t kind, int32_t j, int
             const GmArgs a = gm_args(plan, P);
             hipError_t e;
             if (kind == 0) {
-                e = launch_gm_update(a, j, 1, false, s);
+                e = launch_gm_update(a, j, 1, P.np_gm, false, s);
             } else if (kind == 1) {
                 e = launch_gm_dots(a, j, s);
             } else {

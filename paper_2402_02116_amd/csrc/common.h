@@ -155,23 +155,49 @@ struct SysState {
 };
 
 // ------------------------------------------------------ block reductions --
+// Sums of NV doubles (1, 2, 4 or 8) over a wavefront.  While there is more than
+// one value, a step adds the halves of the wavefront and leaves each half the
+// totals of half of the values, so that 8 values take 10 shuffles instead of
+// 48; every total is added in the order of the plain butterfly.  Returns the
+// total of value lane / (64 / NV).
+template <int NV>
+__device__ __forceinline__ double wave_sum(const double (&v)[NV]) {
+    static_assert(NV == 1 || NV == 2 || NV == 4 || NV == 8, "values");
+    const int lane = threadIdx.x & 63;
+    double a[NV];
+#pragma unroll
+    for (int k = 0; k < NV; ++k) a[k] = v[k];
+    int off = 32;
+#pragma unroll
+    for (int n = NV; n > 1; n /= 2) {
+        const bool hi = (lane & off) != 0;
+#pragma unroll
+        for (int k = 0; k < n / 2; ++k) {
+            const double send = hi ? a[k] : a[k + n / 2], keep = hi ? a[k + n / 2] : a[k];
+            a[k] = keep + __shfl_xor(send, off, 64);
+        }
+        off /= 2;
+    }
+    for (; off > 0; off /= 2) a[0] += __shfl_xor(a[0], off, 64);
+    return a[0];
+}
+
+// The wavefronts' sums of NV doubles into smem[wave][NV]; a barrier must follow.
+template <int NV>
+__device__ __forceinline__ void wave_sums_to(const double (&acc)[NV], double* smem) {
+    const double s = wave_sum<NV>(acc);
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    if (lane % (64 / NV) == 0) smem[wave * NV + lane / (64 / NV)] = s;
+}
+
 // Sum NV doubles over a block of NT threads (NT a multiple of 64), in a fixed
-// order: wave shuffles, then wave partials in index order.  Every thread
+// order: wave sums, then wave partials in index order.  Every thread
 // receives the result.  smem needs NV * NT / 64 doubles.
 template <int NV, int NT>
 __device__ __forceinline__ void block_allreduce(double (&acc)[NV], double* smem) {
     static_assert(NT % 64 == 0, "block must be whole waves");
-#pragma unroll
-    for (int k = 0; k < NV; ++k) {
-#pragma unroll
-        for (int off = 32; off > 0; off >>= 1) acc[k] += __shfl_xor(acc[k], off, 64);
-    }
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     __syncthreads();
-    if (lane == 0) {
-#pragma unroll
-        for (int k = 0; k < NV; ++k) smem[wave * NV + k] = acc[k];
-    }
+    wave_sums_to<NV>(acc, smem);
     __syncthreads();
 #pragma unroll
     for (int k = 0; k < NV; ++k) {

@@ -15,28 +15,16 @@
 
 FW_BEGIN
 // ------------------------------------------------------- block reduce ----
-// Runtime block size (a multiple of 64, at most 256): fixed-order sum of
-// NV doubles; thread 0 receives the total.
+// Fixed-order sums of NV doubles over a block of whole wavefronts into dst
+// (thread k writes value k; smem: NV doubles per wavefront).
 template <int NV>
-__device__ __forceinline__ void block_sum_to0(double (&acc)[NV], double* smem) {
-#pragma unroll
-    for (int k = 0; k < NV; ++k) {
-#pragma unroll
-        for (int off = 32; off > 0; off >>= 1) acc[k] += __shfl_xor(acc[k], off, 64);
-    }
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, nw = blockDim.x >> 6;
-    if (lane == 0) {
-#pragma unroll
-        for (int k = 0; k < NV; ++k) smem[wave * NV + k] = acc[k];
-    }
+__device__ __forceinline__ void block_sum_store(const double (&acc)[NV], double* smem, double* dst) {
+    wave_sums_to<NV>(acc, smem);
     __syncthreads();
-    if (threadIdx.x == 0) {
-#pragma unroll
-        for (int k = 0; k < NV; ++k) {
-            double s = 0.0;
-            for (int w = 0; w < nw; ++w) s += smem[w * NV + k];
-            acc[k] = s;
-        }
+    if (threadIdx.x < NV) {
+        double s = 0.0;
+        for (int w = 0; w < (int)(blockDim.x >> 6); ++w) s += smem[w * NV + threadIdx.x];
+        dst[threadIdx.x] = s;
     }
 }
 
@@ -178,51 +166,53 @@ __global__ __launch_bounds__(256) void k_rows(const cplx* in, cplx* out,
         const int bi = (row0 % rows_per_sys) / F;
         double* rec = ge.part + ((size_t)sys * nb + bi) * kGmRec;
         if constexpr (EPI == EPI_GMRES_R0) {
-            block_sum_to0<kPartialNV>(acc, red);
-            if (tid == 0) {
-                rec[0] = acc[0];
-                rec[1] = acc[1];
-            }
+            const double a[2] = {acc[0], acc[1]};
+            block_sum_store<2>(a, red, rec);
         } else {
-            const size_t base = (size_t)row * N;
+            // Each wavefront leaves its sums of every vector in LDS, with no
+            // barrier in between, so that the wavefronts' loads and sums
+            // overlap.  This pass at 16 vectors, with a block's sum and two
+            // barriers after each pair -> so: 256 x 192 x 16 66.8 -> 33.9 us,
+            // 384^2 x 16 177.6 -> 126.7 (96 x 64 x 4 30.1 -> 23.4).
+            __shared__ double wsum[4][2 * (kGmMax + 1) + 2];
+            const int lane = tid & 63, wave = tid >> 6;
+            // no load under a branch (a wait for all loads before each): threads
+            // without a row read the block's first and add zeros, an odd count
+            // reads the last vector twice and drops the second sums
+            const cplx* __restrict__ vr = ge.V + (size_t)(active ? row : row0) * N + t;
+            if (!active) {
+#pragma unroll
+                for (int m = 0; m < P; ++m) v[0][m] = mkc(0.f, 0.f);
+            }
             for (int l0 = 0; l0 < ge.nv; l0 += 2) {
                 double a[4] = {0.0, 0.0, 0.0, 0.0};
-                if (active) {
+                const cplx* __restrict__ va = vr + (size_t)l0 * ge.vstride;
+                const cplx* __restrict__ vb = l0 + 1 < ge.nv ? va + ge.vstride : va;
 #pragma unroll
-                    for (int m = 0; m < P; ++m) {
-                        const size_t i = base + t + T * m;
-                        const cplx w = v[0][m];
-#pragma unroll
-                        for (int k = 0; k < 2; ++k) {
-                            if (l0 + k < ge.nv) {
-                                const cplx b = ge.V[(size_t)(l0 + k) * ge.vstride + i];
-                                a[2 * k] += (double)b.x * w.x + (double)b.y * w.y;
-                                a[2 * k + 1] += (double)b.x * w.y - (double)b.y * w.x;
-                            }
-                        }
-                    }
+                for (int m = 0; m < P; ++m) {
+                    const cplx w = v[0][m], p = va[T * m], q = vb[T * m];
+                    a[0] += (double)p.x * w.x + (double)p.y * w.y;
+                    a[1] += (double)p.x * w.y - (double)p.y * w.x;
+                    a[2] += (double)q.x * w.x + (double)q.y * w.y;
+                    a[3] += (double)q.x * w.y - (double)q.y * w.x;
                 }
-                block_sum_to0<4>(a, red);
-                if (tid == 0) {
-#pragma unroll
-                    for (int k = 0; k < 4; ++k)
-                        if (2 * l0 + k < 2 * ge.nv) rec[2 * l0 + k] = a[k];
-                }
-                __syncthreads();
+                const double s = wave_sum<4>(a);
+                if ((lane & 15) == 0) wsum[wave][2 * l0 + (lane >> 4)] = s;
+            }
+            __syncthreads();
+            if (tid < 2 * ge.nv) {
+                double s = 0.0;
+                for (int w = 0; w < (int)(blockDim.x >> 6); ++w) s += wsum[w][tid];
+                rec[tid] = s;
             }
         }
     } else if constexpr (EPI >= EPI_BICG_V) {
-        block_sum_to0<kPartialNV>(acc, red);
-        if (tid == 0) {
-            const int nb = rows_per_sys / F;
-            const int bi = (row0 % rows_per_sys) / F;
-            double* dst = partials + ((size_t)sys * nb + bi) * kPartialNV;
-#pragma unroll
-            for (int k = 0; k < kPartialNV; ++k) dst[k] = acc[k];
-            // the iteration is complete up to its solution update
-            if constexpr (EPI == EPI_BICG_T) {
-                if (bi == 0) st[sys].iter += 1;
-            }
+        const int nb = rows_per_sys / F;
+        const int bi = (row0 % rows_per_sys) / F;
+        block_sum_store<kPartialNV>(acc, red, partials + ((size_t)sys * nb + bi) * kPartialNV);
+        // the iteration is complete up to its solution update
+        if constexpr (EPI == EPI_BICG_T) {
+            if (tid == 0 && bi == 0) st[sys].iter += 1;
         }
     }
 }
@@ -582,7 +572,7 @@ __global__ __launch_bounds__(512) void k_cols_sweep(cplx* __restrict__ data, Pro
 // Dynamic LDS above the default limit must be enabled once per kernel.
 template <class K>
 inline hipError_t allow_lds(K kernel, size_t bytes) {
-    if (bytes <= 65536) return hipSuccess;
+    if (bytes <= 61440) return hipSuccess;   // 64 KB less the kernels' static arrays
     return hipFuncSetAttribute(reinterpret_cast<const void*>(kernel),
                                hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes);
 }

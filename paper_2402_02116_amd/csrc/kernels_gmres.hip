@@ -85,26 +85,47 @@ __device__ __forceinline__ void load_coeffs(cplx* c, const double* tot, const Gm
     __syncthreads();
 }
 
-// Hessenberg column j from the two projection passes and n_{j+1}^2, Givens
-// rotations, and the stopping test (one thread).  hre / him: kGmMax + 1
-// doubles each of LDS for the column (a private array indexed at run time
-// would live in scratch memory).
-__device__ void gm_hessenberg(SysState& z, GmSys& g, const double* tot1, const double* tot2, double n2next,
-                              double* hre, double* him) {
+// Hessenberg column being built and the rotations before it (in LDS: a
+// private array indexed at run time would live in scratch memory).
+struct GmCol {
+    double re[kGmMax + 1], im[kGmMax + 1];
+    double cs[kGmMax], sre[kGmMax], sim[kGmMax];
+};
+
+// Entries of Hessenberg column j from the two projection passes and
+// n_{j+1}^2, one per thread, with the rotations: one thread fetching and
+// scaling them one after the other waits for memory at each (this kernel's
+// mean over a cycle of 30 at 256 x 192 x 16 8.9 -> 7.0 us).
+__device__ __forceinline__ void gm_column(GmCol& h, const GmSys& g, const double* tot1, const double* tot2,
+                                          double n2next) {
+    const int j = g.j, l = threadIdx.x;
+    if (l > j + 1) return;
+    const double nj = sqrt(g.n2[j]);
+    if (l <= j) {
+        const double s = sqrt(g.n2[l]) / (g.n2[l] * nj);   // n_l / (n_l^2 n_j)
+        h.re[l] = (tot1[2 * l] + (tot2 ? tot2[2 * l] : 0.0)) * s;
+        h.im[l] = (tot1[2 * l + 1] + (tot2 ? tot2[2 * l + 1] : 0.0)) * s;
+    } else {
+        h.re[l] = sqrt(n2next) / nj;
+        h.im[l] = 0.0;
+    }
+    if (l < j) {
+        h.cs[l] = g.cs[l];
+        h.sre[l] = g.sre[l];
+        h.sim[l] = g.sim[l];
+    }
+}
+
+// Givens rotations of the column and the stopping test (one thread).  The
+// entries above the diagonal stay in h for the caller to store.
+__device__ void gm_hessenberg(SysState& z, GmSys& g, GmCol& h, double n2next) {
     const int j = g.j;
     const int ld = kGmMax + 1;
+    double *hre = h.re, *him = h.im;
     g.n2[j + 1] = n2next;
-    const double nj = sqrt(g.n2[j]);
-    for (int l = 0; l <= j; ++l) {
-        const double s = sqrt(g.n2[l]) / (g.n2[l] * nj);   // n_l / (n_l^2 n_j)
-        hre[l] = (tot1[2 * l] + (tot2 ? tot2[2 * l] : 0.0)) * s;
-        him[l] = (tot1[2 * l + 1] + (tot2 ? tot2[2 * l + 1] : 0.0)) * s;
-    }
-    hre[j + 1] = sqrt(n2next) / nj;
-    him[j + 1] = 0.0;
     // previous rotations: [a; b] <- [c a + s b; -conj(s) a + c b]
     for (int l = 0; l < j; ++l) {
-        const double c = g.cs[l], sr = g.sre[l], si = g.sim[l];
+        const double c = h.cs[l], sr = h.sre[l], si = h.sim[l];
         const double ar = hre[l], ai = him[l], br = hre[l + 1], bi = him[l + 1];
         hre[l] = c * ar + (sr * br - si * bi);
         him[l] = c * ai + (sr * bi + si * br);
@@ -137,10 +158,6 @@ __device__ void gm_hessenberg(SysState& z, GmSys& g, const double* tot1, const d
     g.cs[j] = c;
     g.sre[j] = sr;
     g.sim[j] = si;
-    for (int l = 0; l < j; ++l) {
-        g.rre[j * ld + l] = hre[l];
-        g.rim[j * ld + l] = him[l];
-    }
     g.rre[j * ld + j] = rr;
     g.rim[j * ld + j] = ri;
     // g_{j+1} = -conj(s) g_j, g_j = c g_j
@@ -160,73 +177,105 @@ __device__ void gm_hessenberg(SysState& z, GmSys& g, const double* tot1, const d
     }
 }
 
-// w <- w - sum_{l <= j} c_l w_l in basis slot j + 1, with c from tot (pass 1:
-// the epilogue's projections, pass 2: the re-orthogonalisation's).  With
-// `final`, also a partial ||w||^2 record per block.
-__global__ __launch_bounds__(kGmThreads) void k_gm_update(GmArgs a, int j, int pass, int final) {
+// w <- w - sum_{l <= j} c_l w_l in basis slot j + 1, with c from the
+// projections of the epilogue (pass 1) or of k_gm_dots (pass 2).  With nb_rec,
+// every block sums those nb_rec records itself, in the same order, and the
+// system's first block leaves the sums in tot1 / tot2 for the Hessenberg
+// column; without, k_gm_sum has summed them.  With `final`, also a partial
+// ||w||^2 per block in the last value of the records (the projections are in
+// the ones before, which other blocks may still be reading).
+__global__ __launch_bounds__(kGmThreads) void k_gm_update(GmArgs a, int j, int pass, int nb_rec, int final) {
     __shared__ cplx c[kGmMax + 1];
-    __shared__ double red[4 * 4];
+    __shared__ double sm[kGmThreads];
+    __shared__ double tsum[kGmRec];
     const int nb = gm_nb(a.n);
     const GmView vi = gm_idx(nb);
     if (a.st[vi.sys].status != ST_RUNNING) return;
-    const GmSys& g = a.gs[vi.sys];
-    const double* tot = (pass == 1 ? a.tot1 : a.tot2) + (size_t)vi.sys * kGmRec;
-    load_coeffs(c, tot, g, j + 1);
     const size_t off = (size_t)vi.sys * a.n;
     cplx* w = a.V + (size_t)(j + 1) * a.vstride + off;
-    double acc[4] = {0.0, 0.0, 0.0, 0.0};
+    cplx x[kGmEPT];   // in flight while the records are summed
+    int ix[kGmEPT];   // the last element again past the end: no branch holds a load up
+#pragma unroll
+    for (int e = 0; e < kGmEPT; ++e) {
+        const int i = vi.i0 + e * kGmThreads + threadIdx.x;
+        ix[e] = i < a.n ? i : a.n - 1;
+        x[e] = w[ix[e]];
+    }
+    double* tot = (pass == 1 ? a.tot1 : a.tot2) + (size_t)vi.sys * kGmRec;
+    if (nb_rec) {
+        sum_records(a.part + (size_t)vi.sys * nb_rec * kGmRec, nb_rec, kGmRec, 2 * (j + 1), tsum, sm);
+        if (vi.bi == 0 && threadIdx.x < 2 * (j + 1)) tot[threadIdx.x] = tsum[threadIdx.x];
+        tot = tsum;
+    }
+    load_coeffs(c, tot, a.gs[vi.sys], j + 1);
+    const cplx* __restrict__ v = a.V + off;
+#pragma unroll 4
+    for (int l = 0; l <= j; ++l) {
+        const cplx cl = c[l];
+#pragma unroll
+        for (int e = 0; e < kGmEPT; ++e) x[e] = csub(x[e], cmul(cl, v[ix[e]]));
+        v += a.vstride;
+    }
+    double acc[1] = {0.0};
 #pragma unroll
     for (int e = 0; e < kGmEPT; ++e) {
         const int i = vi.i0 + e * kGmThreads + threadIdx.x;
         if (i < a.n) {
-            cplx x = w[i];
-            for (int l = 0; l <= j; ++l) x = csub(x, cmul(c[l], a.V[(size_t)l * a.vstride + off + i]));
-            st_wt(w + i, x);
-            acc[0] += (double)x.x * x.x + (double)x.y * x.y;
+            st_wt(w + i, x[e]);
+            acc[0] += (double)x[e].x * x[e].x + (double)x[e].y * x[e].y;
         }
     }
     if (!final) return;
-    block_allreduce<4, kGmThreads>(acc, red);
-    if (threadIdx.x == 0) a.part[((size_t)vi.sys * nb + vi.bi) * kGmRec] = acc[0];
+    block_allreduce<1, kGmThreads>(acc, sm);
+    if (threadIdx.x == 0) a.part[((size_t)vi.sys * nb + vi.bi) * kGmRec + kGmRec - 1] = acc[0];
 }
 
-// tot2 = <w_l, w>, l <= j, for w in slot j + 1 (the re-orthogonalisation's
-// projections), summed by each system's last block.
+// Records <w_l, w>, l <= j, for w in slot j + 1 (the re-orthogonalisation's
+// projections).  Each wavefront leaves its sums of every vector in LDS, with
+// one barrier at the end: with the block's sum (and three barriers) after each
+// pair of vectors, no load was in flight over a barrier (256 x 192 x 16, 16
+// vectors: 44.5 -> 32.7 us; 96 x 64: 16.3 -> 7.8).
 __global__ __launch_bounds__(kGmThreads) void k_gm_dots(GmArgs a, int j) {
-    __shared__ double red[4 * 4];
+    __shared__ double wsum[kGmThreads / 64][kGmRec];
     const int nb = gm_nb(a.n);
     const GmView vi = gm_idx(nb);
     if (a.st[vi.sys].status != ST_RUNNING) return;
     const size_t off = (size_t)vi.sys * a.n;
     const cplx* w = a.V + (size_t)(j + 1) * a.vstride + off;
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     cplx x[kGmEPT];
+    int ix[kGmEPT];
 #pragma unroll
     for (int e = 0; e < kGmEPT; ++e) {
         const int i = vi.i0 + e * kGmThreads + threadIdx.x;
-        x[e] = (i < a.n) ? w[i] : mkc(0.f, 0.f);
+        ix[e] = i < a.n ? i : a.n - 1;
+        x[e] = w[ix[e]];
+        if (i >= a.n) x[e] = mkc(0.f, 0.f);
     }
-    double* rec = a.part + ((size_t)vi.sys * nb + vi.bi) * kGmRec;
+#pragma unroll 2
     for (int l0 = 0; l0 <= j; l0 += 2) {
         double acc[4] = {0.0, 0.0, 0.0, 0.0};
 #pragma unroll
         for (int k = 0; k < 2; ++k) {
-            const int l = l0 + k;
-            if (l > j) break;
-            const cplx* v = a.V + (size_t)l * a.vstride + off;
+            // an odd count reads the last vector twice: its sums are not used
+            const int l = l0 + k <= j ? l0 + k : j;
+            const cplx* __restrict__ v = a.V + (size_t)l * a.vstride + off;
 #pragma unroll
             for (int e = 0; e < kGmEPT; ++e) {
-                const int i = vi.i0 + e * kGmThreads + threadIdx.x;
-                if (i < a.n) {
-                    const cplx b = v[i];
-                    acc[2 * k] += (double)b.x * x[e].x + (double)b.y * x[e].y;
-                    acc[2 * k + 1] += (double)b.x * x[e].y - (double)b.y * x[e].x;
-                }
+                const cplx b = v[ix[e]];
+                acc[2 * k] += (double)b.x * x[e].x + (double)b.y * x[e].y;
+                acc[2 * k + 1] += (double)b.x * x[e].y - (double)b.y * x[e].x;
             }
         }
-        block_allreduce<4, kGmThreads>(acc, red);
-        if (threadIdx.x == 0) {
-            for (int k = 0; k < 4 && 2 * l0 + k < 2 * (j + 1); ++k) rec[2 * l0 + k] = acc[k];
-        }
+        const double s = wave_sum<4>(acc);
+        if ((lane & 15) == 0) wsum[wave][2 * l0 + (lane >> 4)] = s;
+    }
+    __syncthreads();
+    if (threadIdx.x < 2 * (j + 1)) {
+        double s = 0.0;
+#pragma unroll
+        for (int q = 0; q < kGmThreads / 64; ++q) s += wsum[q][threadIdx.x];
+        a.part[((size_t)vi.sys * nb + vi.bi) * kGmRec + threadIdx.x] = s;
     }
 }
 
@@ -240,45 +289,64 @@ constexpr int kGmSumThreads = 1024;
 __global__ __launch_bounds__(kGmSumThreads) void k_gm_sum(GmArgs a, int mode, int nb, int j, int cgs2,
                                                       double rtol, int first) {
     __shared__ double sm[kGmSumThreads];
-    __shared__ double hcol[2 * (kGmMax + 1)];
+    __shared__ GmCol h;
     const int sys = blockIdx.x;
     SysState& z = a.st[sys];
     if (z.status != ST_RUNNING) return;
-    const double* rec = a.part + (size_t)sys * nb * kGmRec;
+    // the norms are in the last value of the records
+    const double* rec = a.part + (size_t)sys * nb * kGmRec + (mode == GM_SUM_HESS ? kGmRec - 1 : 0);
     double* tot = (mode == GM_SUM_PROJ1 ? a.tot1 : mode == GM_SUM_PROJ2 ? a.tot2 : a.tot3) + (size_t)sys * kGmRec;
     const int nval = (mode == GM_SUM_HESS) ? 1 : (mode == GM_SUM_BEGIN) ? 2 : 2 * (j + 1);
     sum_records(rec, nb, kGmRec, nval, tot, sm);
-    if (threadIdx.x != 0) return;
-    if (mode == GM_SUM_HESS)
-        gm_hessenberg(z, a.gs[sys], a.tot1 + (size_t)sys * kGmRec, cgs2 ? a.tot2 + (size_t)sys * kGmRec : nullptr,
-                      tot[0], hcol, hcol + kGmMax + 1);
-    else if (mode == GM_SUM_BEGIN)
-        gm_begin(z, a.gs[sys], tot[0], tot[1], rtol, first);
+    if (mode == GM_SUM_HESS) {
+        GmSys& gs = a.gs[sys];
+        const int j0 = gs.j;   // advanced by the first thread
+        const double n2next = tot[0];
+        gm_column(h, gs, a.tot1 + (size_t)sys * kGmRec, cgs2 ? a.tot2 + (size_t)sys * kGmRec : nullptr, n2next);
+        __syncthreads();
+        if (threadIdx.x == 0) gm_hessenberg(z, gs, h, n2next);
+        __syncthreads();
+        if (threadIdx.x < j0) {
+            gs.rre[j0 * (kGmMax + 1) + threadIdx.x] = h.re[threadIdx.x];
+            gs.rim[j0 * (kGmMax + 1) + threadIdx.x] = h.im[threadIdx.x];
+        }
+    } else if (mode == GM_SUM_BEGIN) {
+        if (threadIdx.x == 0) gm_begin(z, a.gs[sys], tot[0], tot[1], rtol, first);
+    }
 }
 
 // ------------------------------------------------------------ cycle end --
-// R y = g by back substitution (k = steps of the cycle); stores y_l / n_l.
-__global__ void k_gm_solve(const SysState* __restrict__ st, GmSys* __restrict__ gs, int nsys) {
-    const int sys = blockIdx.x * blockDim.x + threadIdx.x;
-    if (sys >= nsys || st[sys].status != ST_CYCLE_DONE) return;
+// R y = g by back substitution, column by column (k = steps of the cycle);
+// stores y_l / n_l.  One wavefront per system, lane l with entry l, so that
+// a column is one load and no load waits for a y: by one thread per system, k^2 / 2
+// loads one after the other, a cycle of 30 took 210 us at 16 systems; now
+// 19.7.
+__global__ __launch_bounds__(64) void k_gm_solve(const SysState* __restrict__ st, GmSys* __restrict__ gs) {
+    const int sys = blockIdx.x, lane = threadIdx.x;
+    if (st[sys].status != ST_CYCLE_DONE) return;
     GmSys& g = gs[sys];
     const int k = g.j, ld = kGmMax + 1;
+    const int l = lane < k ? lane : 0;
+    double sr = g.gre[l], si = g.gim[l];
+    const double inv = 1.0 / sqrt(g.n2[l]);
+#pragma unroll 4
     for (int i = k - 1; i >= 0; --i) {
-        double sr = g.gre[i], si = g.gim[i];
-        for (int l = i + 1; l < k; ++l) {
-            const double ar = g.rre[l * ld + i], ai = g.rim[l * ld + i];
-            sr -= ar * g.yre[l] - ai * g.yim[l];
-            si -= ar * g.yim[l] + ai * g.yre[l];
-        }
-        const double dr = g.rre[i * ld + i], di = g.rim[i * ld + i];
+        const double ar = g.rre[i * ld + l], ai = g.rim[i * ld + l];
+        const double dr = __shfl(ar, i, 64), di = __shfl(ai, i, 64);
+        const double tr = __shfl(sr, i, 64), ti = __shfl(si, i, 64);
         const double d = dr * dr + di * di;
-        g.yre[i] = (sr * dr + si * di) / d;
-        g.yim[i] = (si * dr - sr * di) / d;
+        const double yr = (tr * dr + ti * di) / d, yi = (ti * dr - tr * di) / d;
+        if (lane < i) {
+            sr -= ar * yr - ai * yi;
+            si -= ar * yi + ai * yr;
+        } else if (lane == i) {
+            sr = yr;
+            si = yi;
+        }
     }
-    for (int i = 0; i < k; ++i) {
-        const double s = 1.0 / sqrt(g.n2[i]);
-        g.yre[i] *= s;
-        g.yim[i] *= s;
+    if (lane < k) {
+        g.yre[lane] = sr * inv;
+        g.yim[lane] = si * inv;
     }
 }
 
@@ -293,14 +361,26 @@ __global__ __launch_bounds__(kGmThreads) void k_gm_xupdate(cplx* __restrict__ x,
     for (int l = threadIdx.x; l < k; l += blockDim.x) c[l] = mkc((real)g.yre[l], (real)g.yim[l]);
     __syncthreads();
     const size_t off = (size_t)vi.sys * a.n;
+    cplx s[kGmEPT];
+    int ix[kGmEPT];
 #pragma unroll
     for (int e = 0; e < kGmEPT; ++e) {
         const int i = vi.i0 + e * kGmThreads + threadIdx.x;
-        if (i < a.n) {
-            cplx s = x[off + i];
-            for (int l = 0; l < k; ++l) s = cadd(s, cmul(c[l], a.V[(size_t)l * a.vstride + off + i]));
-            st_wt(x + off + i, s);
-        }
+        ix[e] = i < a.n ? i : a.n - 1;
+        s[e] = x[off + ix[e]];
+    }
+    const cplx* __restrict__ v = a.V + off;
+#pragma unroll 4
+    for (int l = 0; l < k; ++l) {
+        const cplx cl = c[l];
+#pragma unroll
+        for (int e = 0; e < kGmEPT; ++e) s[e] = cadd(s[e], cmul(cl, v[ix[e]]));
+        v += a.vstride;
+    }
+#pragma unroll
+    for (int e = 0; e < kGmEPT; ++e) {
+        const int i = vi.i0 + e * kGmThreads + threadIdx.x;
+        if (i < a.n) st_wt(x + off + i, s[e]);
     }
 }
 
@@ -337,10 +417,21 @@ hipError_t launch_gm_sum(const GmArgs& a, int mode, int nb, int j, bool cgs2, do
     return hipGetLastError();
 }
 
-hipError_t launch_gm_update(const GmArgs& a, int j, int pass, bool final, hipStream_t s) {
-    if (j < 0 || j >= kGmMax) return hipErrorInvalidValue;
+// Every block of the update sums the records itself up to this many, instead
+// of a kernel of one block per system before it.  Sum and update at the first
+// step, kernel -> in the update: 4 records (96 x 64) 5.4 -> 3.5 us, 24 (256 x
+// 192 x 16) 8.1 -> 7.3, 32 (256^2) 5.5 -> 4.2, but 96 (384^2 x 16) 21.4 -> 35.4.
+constexpr int kGmFold = 32;
+
+hipError_t launch_gm_update(const GmArgs& a, int j, int pass, int nb_rec, bool final, hipStream_t s) {
+    if (j < 0 || j >= kGmMax || nb_rec < 1) return hipErrorInvalidValue;
+    const bool fold = nb_rec <= kGmFold;
+    if (!fold) {
+        const hipError_t e = launch_gm_sum(a, pass == 1 ? GM_SUM_PROJ1 : GM_SUM_PROJ2, nb_rec, j, true, 0.0, false, s);
+        if (e != hipSuccess) return e;
+    }
     hipLaunchKernelGGL(k_gm_update, dim3(a.nsys * gm_blocks_per_sys(a.n)), dim3(kGmThreads), 0, s, a, j, pass,
-                       final ? 1 : 0);
+                       fold ? nb_rec : 0, final ? 1 : 0);
     return hipGetLastError();
 }
 
@@ -356,7 +447,7 @@ hipError_t launch_gm_report(const SysState* st, int32_t* iters, double* relres, 
 }
 
 hipError_t launch_gm_finish_cycle(cplx* x, const GmArgs& a, hipStream_t s) {
-    hipLaunchKernelGGL(k_gm_solve, per_sys_grid(a.nsys), dim3(64), 0, s, a.st, a.gs, a.nsys);
+    hipLaunchKernelGGL(k_gm_solve, dim3(a.nsys), dim3(64), 0, s, a.st, a.gs);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
     hipLaunchKernelGGL(k_gm_xupdate, dim3(a.nsys * gm_blocks_per_sys(a.n)), dim3(kGmThreads), 0, s, x, a);

@@ -295,7 +295,8 @@ hipError_t launch_gm_init(SysState* st, GmSys* gs, int nsys, int maxit, int m, h
 enum GmSum : int { GM_SUM_PROJ1 = 0, GM_SUM_PROJ2 = 1, GM_SUM_HESS = 2, GM_SUM_BEGIN = 3 };
 hipError_t launch_gm_sum(const GmArgs& a, int mode, int nb, int j, bool cgs2, double rtol, bool first,
                          hipStream_t s);
-hipError_t launch_gm_update(const GmArgs& a, int j, int pass, bool final, hipStream_t s);
+// Sums the nb_rec projection records per system too.
+hipError_t launch_gm_update(const GmArgs& a, int j, int pass, int nb_rec, bool final, hipStream_t s);
 hipError_t launch_gm_dots(const GmArgs& a, int j, hipStream_t s);
 hipError_t launch_gm_finish_cycle(cplx* x, const GmArgs& a, hipStream_t s);
 hipError_t launch_gm_report(const SysState* st, int32_t* iters, double* relres, int nsys, hipStream_t s);

@@ -207,15 +207,10 @@ __global__ __launch_bounds__(512) void k_plane_inv(const cplx* __restrict__ in, 
         }
     }
     if (!need_a) return;   // uniform: no records
-    block_sum_to0<kPartialNV>(acc, red);
-    if (threadIdx.x == 0) {
-        const int nb = planes_per_sys / G, bi = blk - sys * nb;
-        double* d = partials + ((size_t)sys * nb + bi) * kPartialNV;
-#pragma unroll
-        for (int k = 0; k < kPartialNV; ++k) d[k] = acc[k];
-        // the iteration is complete up to its solution update
-        if (epi == EPI_BICG_T && bi == 0) st[sys].iter += 1;
-    }
+    const int nb = planes_per_sys / G, bi = blk - sys * nb;
+    block_sum_store<kPartialNV>(acc, red, partials + ((size_t)sys * nb + bi) * kPartialNV);
+    // the iteration is complete up to its solution update
+    if (epi == EPI_BICG_T && bi == 0 && threadIdx.x == 0) st[sys].iter += 1;
 }
 
 // Launches both passes of one (NX, NY).

@@ -134,3 +134,25 @@ def test_frechet_and_adjoint_through_gmres_match_oracle():
     gg = _np(g[0])
     for k in range(5):
         assert _rel(gg[k], g_ref[k]) < FIELD_TOL, k
+
+
+@pytest.mark.parametrize("nx,nz,restart,cgs2", [(24, 16, 1, True), (24, 16, 32, False), (48, 24, 31, True),
+                                                (64, 192, 2, False), (256, 96, 32, True), (96, 256, 7, True)])
+def test_gmres_cycle_edges(nx, nz, restart, cgs2):
+    """Odd and even basis sizes up to the longest cycle, vectors that end
+    inside a block, and few and many projection records per system (summed by
+    the update itself or by the kernel before it), against the oracle."""
+    from paper_2402_02116_amd.plan import Plan
+    print(f"gmres cycle {nx}x{nz} restart={restart} cgs2={cgs2}", flush=True)
+    p, maps = _case(nx, nz, 2, amp=0.05)
+    plan = Plan([p])
+    plan.set_contrast(0, maps)
+    plan.set_krylov("gmres", restart=restart, cgs2=cgs2)
+    src, f = W.surface_sources(nx, 2, iz=nz // 4)
+    u0 = plan.incident(src, f)
+    res = plan.solve(u0, rtol=1e-6, maxit=2000)
+    assert res.status == 0 and np.all(res.relres <= 2e-6), (res.status, res.relres, res.iters)
+    P = _oracle(p, maps)
+    b, x = _np(plan.view(u0, 0)), _np(plan.view(res.x, 0))
+    # the accepted residual (2 rtol) plus the fp32 rounding of A
+    assert _rel(P.apply(x), b) <= 3e-6
