@@ -682,7 +682,7 @@ def normal_cg(a):
 # the spectrum and u and writing A u
 PASS3_BYTES = (48.0, 48.0, 48.0, 72.0)
 PASS3_NAMES = ("k_stencil3 (contrast stencil, six strains)", "k_plane_fwd (x and y transforms)",
-               "k_axis (z with 3x3 G_hat)", "k_plane_inv (inverse x and y transforms + LS epilogue)")
+               "k_green3 (z with 3x3 G_hat)", "k_plane_inv (inverse x and y transforms + LS epilogue)")
 
 
 def hess3d(a):
